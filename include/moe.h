@@ -172,9 +172,8 @@ moe_status moe_route_topk_ex(const float* logits, int T, int E, int k, int n_sha
  *   x         bf16 [T, H]      w_router  bf16 [E, H]
  *   logits    fp32 [T, E] (written if not NULL)
  *   topk_ids, topk_w as moe_route_topk
- * With a logits buffer and T < 1024 the call runs moe_router_logits and
- * moe_route_topk_ex instead (two kernels; faster for few tokens, where a
- * fused workgroup streams the whole router matrix for a handful of tokens).
+ * With a logits buffer the call runs moe_router_logits and
+ * moe_route_topk_ex instead (two kernels, the faster way at every size).
  * The fused workgroup holds 32 tokens' logits of all E experts in LDS
  * (32 * (E rounded up to 64, plus 1) * 4 bytes: 131 KB at E = 1024).
  * Requires H % 128 == 0 plus the requirements of moe_route_topk_ex

@@ -6,39 +6,300 @@
 // recovery / Later numerical and integration repairs). Lanes 0..k-1 keep pick
 // j = lane; the renormalised softmax weights are formed from them with the
 // denominator summed in pick order.
-#include "moe_dev.h"
+#include "gemm_common.h"
 #include "moe_launch.h"
+
+#include <type_traits>
 
 namespace moe {
 
-// logits[t, e] = sum_h x[t, h] * wr[e, h]; one wave per (t, e). Each lane
-// accumulates 8 consecutive h per step (fmaf, fixed order), then a fixed
-// butterfly sums the 64 lane partials.
-__global__ __launch_bounds__(256) void router_logits_kernel(const uint16_t* __restrict__ x,
+// logits[t, e] = sum_h x[t, h] * wr[e, h] on the bf16 matrix cores
+// (16x16x32: exact products, fp32 sums). A workgroup owns a tile of 16 MB
+// tokens x 16 NB experts and its 8 waves split the K steps of 32 into 16 runs:
+// wave w takes runs 2w and 2w + 1, run r the steps [r n / 16, (r + 1) n / 16),
+// one after the other with the first run's sums kept in LDS. Two steps'
+// products are summed in the matrix core from zero and then added to the run's
+// sum, and the 16 sums are added in a fixed order (see the end). Longer chains
+// in the matrix core lose bits (it truncates: relative error 1.33e-7 with one
+// chain per wave at H = 4096); this order is at least as exact as 64 fma chains
+// and a butterfly. The split depends on H alone, so a token's logits depend
+// neither on the batch nor on the tile size.
+// Bound by the loads: lane l reads 16 bytes of row l % 16 at K 8 (l / 16), so
+// one load covers 64 bytes of 16 rows, and two steps of them are in flight
+// while two are multiplied (U step pairs a buffer). A row is read E / (16 NB)
+// times instead of E times.
+typedef __bf16 v8bf_l __attribute__((ext_vector_type(8)));
+
+template <int MB, int NB, int U>
+__global__ __launch_bounds__(512) void router_logits_kernel(const uint16_t* __restrict__ x,
                                                             const uint16_t* __restrict__ wr, int T,
                                                             int H, int E,
                                                             float* __restrict__ logits) {
-  const long wave = ((long)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const int lane = threadIdx.x % kWave;
-  if (wave >= (long)T * E) return;
-  const int t = (int)(wave / E), e = (int)(wave % E);
-  const uint16_t* xr = x + (size_t)t * H;
-  const uint16_t* wrow = wr + (size_t)e * H;
-  float acc = 0.0f;
-  for (int h = lane * 8; h < H; h += kWave * 8) {
-    const uint4 xv = *reinterpret_cast<const uint4*>(xr + h);
-    const uint4 wv = *reinterpret_cast<const uint4*>(wrow + h);
-    const uint32_t xs[4] = {xv.x, xv.y, xv.z, xv.w};
-    const uint32_t ws[4] = {wv.x, wv.y, wv.z, wv.w};
+  constexpr int NT = MB * NB;
+  extern __shared__ __attribute__((aligned(16))) uint8_t rl_lds[];
+  v4f* red = reinterpret_cast<v4f*>(rl_lds);  // [8][NT][64]
+  const int nc = (E + 16 * NB - 1) / (16 * NB);
+  const int t0 = (int)(blockIdx.x / nc) * 16 * MB, e0 = (int)(blockIdx.x % nc) * 16 * NB;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int lane = threadIdx.x % kWave, c16 = lane & 15, g = lane >> 4;
+  // operand rows (clamped to valid rows; the extra results are never stored)
+  // as a uniform base and a lane offset
+  const uint8_t* xb = reinterpret_cast<const uint8_t*>(x + (size_t)t0 * H);
+  const uint8_t* eb = reinterpret_cast<const uint8_t*>(wr + (size_t)e0 * H);
+  using Off = std::conditional_t<NT == 1, size_t, uint32_t>;  // NT == 1 takes any H
+  Off ao[MB], bo[NB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      acc = fmaf(bf16_to_f32(xs[i] & 0xffffu), bf16_to_f32(ws[i] & 0xffffu), acc);
-      acc = fmaf(bf16_to_f32(xs[i] >> 16), bf16_to_f32(ws[i] >> 16), acc);
+  for (int m = 0; m < MB; ++m) ao[m] = (Off)min(16 * m + c16, T - 1 - t0) * H * 2 + 16 * g;
+#pragma unroll
+  for (int n = 0; n < NB; ++n) bo[n] = (Off)min(16 * n + c16, E - 1 - e0) * H * 2 + 16 * g;
+  struct Step {
+    v8bf_l a[MB], b[NB];
+  };
+  struct Buf {
+    Step s[2 * U];
+  };
+  v4f acc[MB][NB];
+  auto load1 = [&](Step& f, int s) {
+    const uint8_t *xk = xb + (size_t)s * 64, *ek = eb + (size_t)s * 64;
+#pragma unroll
+    for (int m = 0; m < MB; ++m) f.a[m] = *reinterpret_cast<const v8bf_l*>(xk + ao[m]);
+#pragma unroll
+    for (int n = 0; n < NB; ++n) f.b[n] = *reinterpret_cast<const v8bf_l*>(ek + bo[n]);
+  };
+  auto load = [&](Buf& f, int s) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 2 * U; ++u) load1(f.s[u], s + u);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mma = [&](const Buf& f) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          const Step &p = f.s[2 * u], &q = f.s[2 * u + 1];
+          v4f d = v4f{0.f, 0.f, 0.f, 0.f};
+          d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p.a[m], p.b[n], d, 0, 0, 0);
+          d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q.a[m], q.b[n], d, 0, 0, 0);
+          acc[m][n] += d;
+        }
+  };
+  auto mma1 = [&](const Step& p) {
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const v4f d = v4f{0.f, 0.f, 0.f, 0.f};
+        acc[m][n] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(p.a[m], p.b[n], d, 0, 0, 0);
+      }
+  };
+  const int nst = (H + 31) / 32, whole = H / 32;  // steps, and those wholly inside H
+  Buf f0, f1;
+  for (int r = 0; r < 2; ++r) {
+    const int s_hi = (int)((long)(2 * w + r + 1) * nst / 16);
+    const int full = min(s_hi, whole);
+    int s = (int)((long)(2 * w + r) * nst / 16);
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int n = 0; n < NB; ++n) acc[m][n] = v4f{0.f, 0.f, 0.f, 0.f};
+    const int n = (full - s) / (2 * U);  // buffers of this run
+    if (n > 0) {
+      load(f0, s);
+      int i = 0;
+      for (; i + 2 < n; i += 2) {  // f0 holds buffer i
+        load(f1, s + 2 * U * (i + 1));
+        mma(f0);
+        load(f0, s + 2 * U * (i + 2));
+        mma(f1);
+      }
+      if (i + 1 < n) {
+        load(f1, s + 2 * U * (i + 1));
+        mma(f0);
+        mma(f1);
+      } else {
+        mma(f0);
+      }
+      s += 2 * U * n;
+    }
+    for (; s < full; ++s) {
+      load1(f0.s[0], s);
+      mma1(f0.s[0]);
+    }
+    if (s < s_hi) {  // the last, partial step: H % 8 == 0, so a lane's 8 elements are in or out
+      const bool in = 32 * s + 8 * g < H;
+      Step& q = f0.s[0];
+#pragma unroll
+      for (int m = 0; m < MB; ++m) q.a[m] = v8bf_l{};
+#pragma unroll
+      for (int n2 = 0; n2 < NB; ++n2) q.b[n2] = v8bf_l{};
+      if (in) load1(q, s);
+      mma1(q);
+    }
+    if (r == 0) {
+#pragma unroll
+      for (int i = 0; i < NT; ++i) red[(w * NT + i) * kWave + lane] = acc[i / NB][i % NB];
     }
   }
+  // run sums: wave w forms p_w = r_{2w} + r_{2w+1}; then
+  // ((p0 + p1) + (p2 + p3)) + ((p4 + p5) + (p6 + p7)) by all threads
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) acc += shfl_xor_f(acc, m);
-  if (lane == 0) logits[(size_t)t * E + e] = acc;
+  for (int i = 0; i < NT; ++i) {
+    v4f* q = red + (w * NT + i) * kWave + lane;
+    *q = *q + acc[i / NB][i % NB];
+  }
+  __syncthreads();
+  // D: lane l, element q of block (m, n) = token 16 m + 4 (l / 16) + q, expert 16 n + l % 16
+  for (int i = w; i < NT; i += 8) {
+    v4f p[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p[j] = red[(j * NT + i) * kWave + lane];
+    const v4f d = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+    const int t = t0 + 16 * (i / NB) + 4 * g, e = e0 + 16 * (i % NB) + c16;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (t + q < T && e < E) logits[(size_t)(t + q) * E + e] = d[q];
+  }
+}
+
+// The same logits, bit for bit, for many tokens (H % 2048 == 0, so every run
+// is the same number of step pairs, and an even one): a tile of 64 tokens x 64 NB experts whose
+// operands are staged in LDS, each of the 8 waves owning 32 x 16 NB outputs over
+// the whole of K. Direct loads put the 64 lanes of an instruction on 16 rows,
+// no two neighbours on one cache line, and the address unit takes a line a
+// lane: 64 clocks for 1 KiB. A DMA instruction here reads 128 bytes of 8 rows in
+// lane order. K steps of 64 go through a ring of four stages (48 KiB at NB = 1,
+// 96 KiB at NB = 2); every wave issues 1 + NB instructions a stage, so one wait
+// counts exactly. 16-byte chunk c of row r sits at c ^ ((r >> 1) & 7), which
+// spreads the operand reads over the banks. The 16 run sums meet in the order
+// of the kernel above through four levels of kept sums.
+// LDS ring stages: as many as fit a CU (128 KiB at NB = 1, 144 KiB at NB = 2).
+constexpr int rl_ring(int nb) { return nb == 1 ? 8 : 6; }
+
+template <int NB>
+__global__ __launch_bounds__(512) void router_logits_lds_kernel(const uint16_t* __restrict__ x,
+                                                                const uint16_t* __restrict__ wr,
+                                                                int T, int H, int E,
+                                                                float* __restrict__ logits) {
+  constexpr int kRows = 64 + 64 * NB, kStage = kRows * 128, kPer = 1 + NB;
+  constexpr int kRlRing = rl_ring(NB);
+  extern __shared__ __attribute__((aligned(16))) uint8_t rl_lds[];
+  // the tiles of one token block run on one XCD, which then reads its rows once
+  const int lin = xcd_remap(blockIdx.x, gridDim.x), nc = (E + 64 * NB - 1) / (64 * NB);
+  const int t0 = lin / nc * 64, e0 = lin % nc * 64 * NB;
+  if (t0 >= T) return;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int lane = threadIdx.x % kWave, c16 = lane & 15, g = lane >> 4;
+  const uint8_t* xb = reinterpret_cast<const uint8_t*>(x + (size_t)t0 * H);
+  const uint8_t* eb = reinterpret_cast<const uint8_t*>(wr + (size_t)e0 * H);
+  const uint32_t ring = __builtin_amdgcn_readfirstlane(lds_addr(rl_lds));
+  // DMA instruction i of the tile covers LDS rows 8 i .. 8 i + 7 (64 token
+  // rows, then the expert rows; rows past the end repeat the last valid one)
+  const int lr = lane >> 3;
+  uint32_t ao, bo[NB];
+  {
+    const int r = 8 * w + lr;
+    ao = (uint32_t)min(r, T - 1 - t0) * (uint32_t)(2 * H) + 16 * ((lane & 7) ^ ((r >> 1) & 7));
+  }
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    const int r = 8 * (NB * w + n) + lr;
+    bo[n] = (uint32_t)min(r, E - 1 - e0) * (uint32_t)(2 * H) + 16 * ((lane & 7) ^ ((r >> 1) & 7));
+  }
+  const int nst = H / 64;
+  auto issue = [&](int k) {  // past the last stage the slot gets the last stage again
+    const uint32_t slot = ring + (uint32_t)(k % kRlRing) * kStage;
+    const size_t o = (size_t)min(k, nst - 1) * 128;
+    sdma16(xb + o, ao, slot + 1024 * w);
+#pragma unroll
+    for (int n = 0; n < NB; ++n) sdma16(eb + o, bo[n], slot + 8192 + 1024 * (NB * w + n));
+  };
+  // operand reads of this lane: token rows 32 (w & 1) + 16 m + c16, expert rows
+  // 16 NB (w >> 1) + 16 n + c16, chunk 4 s + g
+  const int tr = 32 * (w & 1) + c16, er = 16 * NB * (w >> 1) + c16;
+  v4f acc[2][NB], l0[2][NB], l1[2][NB], l2[2][NB], l3[2][NB];
+#pragma unroll
+  for (int k = 0; k < kRlRing - 2; ++k) issue(k);
+  const int per = nst / 16;  // stages per run
+  int k = 0;
+  for (int r = 0; r < 16; ++r) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int n = 0; n < NB; ++n) acc[m][n] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < per; j += 2, k += 2) {
+      // this wave's part of stages k and k + 1 landed; after the barrier every
+      // wave's has, and every wave has read stages k - 2 and k - 1
+      tvmcnt_s<(kRlRing - 4) * kPer>();
+      asm volatile("s_barrier" ::: "memory");
+      issue(k + kRlRing - 2);
+      issue(k + kRlRing - 1);
+      v8bf_l a[4][2], b[4][NB];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const uint8_t* st = rl_lds + ((k + s / 2) % kRlRing) * kStage;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const int row = tr + 16 * m;
+          a[s][m] = *reinterpret_cast<const v8bf_l*>(st + row * 128 +
+                                                     16 * ((4 * (s & 1) + g) ^ ((row >> 1) & 7)));
+        }
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          const int row = er + 16 * n;
+          b[s][n] = *reinterpret_cast<const v8bf_l*>(st + 8192 + row * 128 +
+                                                     16 * ((4 * (s & 1) + g) ^ ((row >> 1) & 7)));
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 4; s += 2)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+          for (int n = 0; n < NB; ++n) {
+            v4f d = v4f{0.f, 0.f, 0.f, 0.f};
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s][m], b[s][n], d, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s + 1][m], b[s + 1][n], d, 0, 0, 0);
+            acc[m][n] += d;
+          }
+    }
+    // runs in pairs, pairs of pairs, ..: a binary counter of kept sums
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        v4f& s = acc[m][n];
+        if ((r & 1) == 0) {
+          l0[m][n] = s;
+        } else {
+          s = l0[m][n] + s;
+          if ((r & 2) == 0) {
+            l1[m][n] = s;
+          } else {
+            s = l1[m][n] + s;
+            if ((r & 4) == 0) {
+              l2[m][n] = s;
+            } else {
+              s = l2[m][n] + s;
+              if ((r & 8) == 0) l3[m][n] = s;
+              else s = l3[m][n] + s;
+            }
+          }
+        }
+      }
+  }
+  tvmcnt_s<0>();  // the ring's last (repeated) loads
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      const int t = t0 + 32 * (w & 1) + 16 * m + 4 * g, e = e0 + er + 16 * n;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (t + q < T && e < E) logits[(size_t)(t + q) * E + e] = acc[m][n][q];
+    }
 }
 
 // EPL = experts held per lane (ceil(E / 64) rounded up to a power of two).
@@ -392,12 +653,39 @@ hipError_t launch_route_topk_ex(const float* logits, int T, int E, int k, int n_
   return hipGetLastError();
 }
 
+template <int MB, int NB, int U>
+static void launch_rl(const uint16_t* x, const uint16_t* wr, int T, int H, int E, float* logits,
+                      hipStream_t s) {
+  const int n = ((E + 16 * NB - 1) / (16 * NB)) * ((T + 16 * MB - 1) / (16 * MB));
+  hipLaunchKernelGGL((router_logits_kernel<MB, NB, U>), dim3(n), dim3(512),
+                     (size_t)8 * MB * NB * kWave * sizeof(v4f), s, x, wr, T, H, E, logits);
+}
+
 hipError_t launch_router_logits(const uint16_t* x, const uint16_t* wr, int T, int H, int E,
                                 float* logits, hipStream_t s) {
-  const long waves = (long)T * E;
-  if (waves == 0) return hipSuccess;
-  const int blocks = (int)((waves * kWave + 255) / 256);
-  hipLaunchKernelGGL(router_logits_kernel, dim3(blocks), dim3(256), 0, s, x, wr, T, H, E, logits);
+  if (T == 0) return hipSuccess;
+  // All variants give the same bits; the tile only spreads the work. Measured
+  // at H = 4096, E = 256 (us a call, launch gaps included; one fma chain per
+  // logit before): 64 tokens 9.4 (11.2), 333: 16.5 with 32 x 32 tiles, 20.9
+  // from LDS (48); 1024: 18.0 and 21.1 (141); 2048: 33.5 and 21.7 (263);
+  // 8192: 69 with 64 x 64 tiles and 31 from LDS (1010).
+  const long tiles = (long)((T + 15) / 16) * ((E + 15) / 16);  // of 16 x 16
+  if (tiles > 1024 && H % 2048 == 0 && H < (1 << 24)) {
+    const int nb = (long)((T + 63) / 64) * ((E + 127) / 128) >= 192 ? 2 : 1;  // fill the CUs
+    const int n = ((E + 64 * nb - 1) / (64 * nb)) * ((T + 63) / 64);
+    const dim3 grid((n + 7) / 8 * 8);
+    const size_t lds = (size_t)rl_ring(nb) * (64 + 64 * nb) * 128;
+    if (nb == 2)
+      hipLaunchKernelGGL(router_logits_lds_kernel<2>, grid, dim3(512), lds, s, x, wr, T, H, E, logits);
+    else
+      hipLaunchKernelGGL(router_logits_lds_kernel<1>, grid, dim3(512), lds, s, x, wr, T, H, E, logits);
+  } else if (tiles <= 512 || H >= (1 << 24)) {  // (the larger tiles hold 32-bit row offsets)
+    launch_rl<1, 1, 2>(x, wr, T, H, E, logits, s);
+  } else if (tiles <= 2048) {
+    launch_rl<2, 2, 2>(x, wr, T, H, E, logits, s);
+  } else {
+    launch_rl<4, 4, 1>(x, wr, T, H, E, logits, s);
+  }
   return hipGetLastError();
 }
 

@@ -178,3 +178,43 @@ def test_router_topk_rejects(m):
     with pytest.raises(m.MoeError):
         m.moe_router_topk(torch.zeros((4, 192), dtype=torch.bfloat16, device="cuda"),
                           torch.zeros((16, 192), dtype=torch.bfloat16, device="cuda"), 2)
+
+
+# ------------------------------------------------------- router projection (a1)
+@pytest.mark.parametrize("T,H,E", [
+    (1, 4096, 256), (17, 40, 5), (64, 8, 1), (33, 1544, 33),        # 16 x 16 tiles, partial K steps
+    (600, 512, 256), (1023, 264, 250),                              # 32 x 32
+    (2100, 264, 260),                                               # 64 x 64
+    (1100, 2048, 256), (3000, 4096, 65), (8200, 2048, 200),         # LDS, one and two column blocks
+])
+def test_router_logits_paths(m, T, H, E):
+    """Every tile size against fp64, and the same bits whatever the batch."""
+    xb, wb = _router_case(T, H, E, T + H + E)
+    log(f"router logits T={T} H={H} E={E}")
+    x = torch.from_numpy(xb.view(np.int16)).cuda().view(torch.bfloat16)
+    wr = torch.from_numpy(wb.view(np.int16)).cuda().view(torch.bfloat16)
+    lg = m.moe_router_logits(x, wr)
+    head = m.moe_router_logits(x[:7].contiguous(), wr)
+    tail = m.moe_router_logits(x[-3:].contiguous(), wr)
+    torch.cuda.synchronize()
+    assert torch.equal(lg[:7], head) and torch.equal(lg[-3:], tail)
+    ref = omoe.router_logits(xb, wb)
+    mag = np.abs(omoe.mx.bf16_to_f64(xb)) @ np.abs(omoe.mx.bf16_to_f64(wb)).T
+    # H / 32 truncating matrix-core sums, H / 64 adds of them, 5 levels of run sums
+    assert np.all(np.abs(lg.cpu().numpy() - ref) <= (H / 16 + 16) * 2.0 ** -24 * mag + 1e-30)
+
+
+@pytest.mark.parametrize("T,H,E,k", [(1, 256, 256, 8), (37, 512, 100, 7), (1500, 512, 64, 4),
+                                     (1100, 256, 1024, 8)])
+def test_router_topk_without_logits_buffer(m, T, H, E, k):
+    """The one-kernel form (no logits buffer): the picks of the fp64 logits but
+    for near ties."""
+    xb, wb = _router_case(T, H, E, T + H + E)
+    log(f"fused router, no logits buffer T={T} H={H} E={E}")
+    ids, w = m.moe_router_topk(torch.from_numpy(xb.view(np.int16)).cuda().view(torch.bfloat16),
+                               torch.from_numpy(wb.view(np.int16)).cuda().view(torch.bfloat16), k, 1)
+    torch.cuda.synchronize()
+    ids64, w64 = omoe.route_topk_ex(omoe.router_logits(xb, wb), k, 1)
+    diff = (ids.cpu().numpy() != ids64).any(axis=1)
+    assert diff.mean() <= 1e-2
+    assert np.all(np.abs(w.cpu().numpy() - w64)[~diff] <= 1e-4 * np.abs(w64[~diff]) + 1e-7)
