@@ -86,6 +86,9 @@ enum {
   MOE_VARIANT_BF16 = 3,   /* MOE_ACT_BF16: LDS-tiled bf16 geometry (many rows per expert) */
   MOE_VARIANT_MIXED = 4,  /* tiled stage 1, streaming stage 2 (I not a multiple of 512) */
   MOE_VARIANT_BF16_STREAM = 5, /* MOE_ACT_BF16: weight-streaming bf16 geometry (few rows) */
+  MOE_VARIANT_BLOCK = 7,  /* row-block geometry for a middling number of rows per expert (64-row
+                             tiles, weights streamed to registers), in either stage or both; a
+                             stage whose K it does not take streams */
   MOE_VARIANT_SHORT = 6   /* stage 2 on the short-K geometry (I = 128 or 256, many rows per
                              expert: the whole K extent of a 128-row tile in LDS); stage 1
                              tiled when H is a multiple of 512, else streaming */
@@ -275,7 +278,8 @@ moe_status moe_quantize_act(const uint16_t* x, int rows, int K, moe_act_format f
  * Requires T >= 0, H > 0, I > 0, H % 128 == 0, I % 128 == 0,
  * 1 <= NE <= MOE_MAX_EXPERTS_TOTAL, 1 <= k_total <= MOE_MAX_K_TOTAL.
  * The geometry (MOE_VARIANT_*) is chosen per stage from T * k_total / NE and
- * the stage's K extent (the tiled K loop takes multiples of 512) and reported
+ * the stage's K extent (the tiled and row-block K loops take multiples of 512,
+ * the latter also 256) and reported
  * by moe_last_variant(); under MOE_ACT_BF16 from T * k_total / NE alone
  * (tiled from 64 rows per expert on average, both stages alike).
  * The kernels address activation rows and one expert's weights with 32-bit

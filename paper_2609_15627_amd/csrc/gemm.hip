@@ -92,7 +92,7 @@ __device__ __forceinline__ void build_tiles(const int32_t* __restrict__ offsets,
     }
     const int j = i - start[lo];
     const int r0 = offsets[lo] + j * BM;
-    tiles[i] = make_int4(lo, r0, min(BM, offsets[lo + 1] - r0), 0);
+    tiles[i] = make_int4(lo, r0, min(BM, offsets[lo + 1] - r0), start[lo + 1] - start[lo]);
   }
 }
 
@@ -176,11 +176,18 @@ static int max_lds_per_block() {
 // or 256, stage 2 runs on the short-K geometry (a tile's whole K extent in
 // LDS); the weight-streaming geometry otherwise. So a shape like the TP8
 // expert shard (I = 256) runs stage 1 tiled and stage 2 short-K.
+// Between kBlockMinRows and kTiledMinRows rows per expert the stages take the
+// row-block geometry (K = 256 or a multiple of 512; stage 2: H a multiple of
+// 256). Measured at H = 4096, I = 2048, 256 + 1 experts, MXFP8, layer us:
+// streaming / row-block 582 / 612 at 5.6 rows, 643 / 633 at 11.7, 1346 / 789 at
+// 38; row-block / tiled 900 / 927 at 53, 990 / 967 at 70.
 constexpr int kTiledMinRows = 64;
+constexpr int kBlockMinRows = 10;
 
 struct Geometry {
   bool s1_tiled, s2_tiled;
   bool s2_short;  // stage 2 on the short-K geometry (I = 128 or 256, many rows)
+  bool s1_block, s2_block;  // the row-block geometry (before the others)
 };
 
 static Geometry geometry(const GemmArgs& a) {
@@ -196,13 +203,22 @@ static Geometry geometry(const GemmArgs& a) {
   const bool s2_tiled = many && tiled_ok(a.H, a.I);
   const bool s2_short = rows && !s2_tiled && short_k_ok(a.I) && a.H % 256 == 0 &&
                         (size_t)max_lds_per_block() >= short_lds_bytes(a.fmt, a.I);
-  return Geometry{many && tiled_k_ok(a.H) && a.I % 128 == 0, s2_tiled, s2_short};
+  Geometry g{many && tiled_k_ok(a.H) && a.I % 128 == 0, s2_tiled, s2_short, false, false};
+  // Shapes that the fused down + combine kernel takes stay on the streaming
+  // geometry, whose sums it repeats.
+  if (!rows && A >= (long)kBlockMinRows * a.NE &&
+      fused_lds_bytes(a.T, a.k_total, a.I) > (size_t)max_lds_per_block()) {
+    g.s1_block = block_k_ok(a.H) && (size_t)max_lds_per_block() >= block_lds_bytes(a.fmt, a.H);
+    g.s2_block = block_k_ok(a.I) && a.H % 256 == 0 &&
+                 (size_t)max_lds_per_block() >= block_lds_bytes(a.fmt, a.I);
+  }
+  return g;
 }
 
 bool fused_combine_ok(const GemmArgs& a) {
   const Geometry g = geometry(a);
-  return a.fmt != kFmtBf16 && !g.s1_tiled && !g.s2_tiled && !g.s2_short &&
-         fused_lds_bytes(a.T, a.k_total, a.I) <= (size_t)max_lds_per_block();
+  return a.fmt != kFmtBf16 && !g.s1_tiled && !g.s2_tiled && !g.s2_short && !g.s1_block &&
+         !g.s2_block && fused_lds_bytes(a.T, a.k_total, a.I) <= (size_t)max_lds_per_block();
 }
 
 static hipError_t launch_geometry(const GemmArgs& a, const GemmWorkspace& w, int stages,
@@ -210,8 +226,8 @@ static hipError_t launch_geometry(const GemmArgs& a, const GemmWorkspace& w, int
   const bool bf = a.fmt == kFmtBf16;
   const long A = (long)a.T * a.k_total;
   const int TR = tiled_rows(A, a.NE);
-  const int BM1 = g.s1_tiled ? (bf ? bf16_rows() : TR) : (bf ? bf16_stream_rows() : 16);
-  const int BM2 = g.s2_tiled ? (bf ? bf16_rows() : TR)
+  const int BM1 = g.s1_block ? block_rows() : g.s1_tiled ? (bf ? bf16_rows() : TR) : (bf ? bf16_stream_rows() : 16);
+  const int BM2 = g.s2_block ? block_rows() : g.s2_tiled ? (bf ? bf16_rows() : TR)
                              : (g.s2_short ? short_rows() : (bf ? bf16_stream_rows() : 16));
   uint8_t* lists = a.ws + w.off[4];
   const TileArgs t1 = tile_list(lists, A, a.NE, BM1);
@@ -250,6 +266,7 @@ static hipError_t launch_geometry(const GemmArgs& a, const GemmWorkspace& w, int
     p1.k_total = a.k_total;
     p1.t = t1;
     if (bf) (g.s1_tiled ? launch_s1_bf16 : launch_s1_bf16_stream)(p1, t1.mt_bound, s);
+    else if (g.s1_block) launch_s1_block(p1, t1.mt_bound, a.fmt, s);
     else if (g.s1_tiled) launch_s1_tiled(p1, t1.mt_bound, a.fmt, TR, s);
     else launch_s1_stream(p1, t1.mt_bound, a.fmt, s);
   }
@@ -266,6 +283,7 @@ static hipError_t launch_geometry(const GemmArgs& a, const GemmWorkspace& w, int
     p2.t = t2;
     if (a.out) launch_s2c_stream(S2CArgs{p2, a.topk_w, a.out, a.T, a.k_total}, a.fmt, s);
     else if (bf) (g.s2_tiled ? launch_s2_bf16 : launch_s2_bf16_stream)(p2, t2.mt_bound, s);
+    else if (g.s2_block) launch_s2_block(p2, t2.mt_bound, a.fmt, s);
     else if (g.s2_tiled) launch_s2_tiled(p2, t2.mt_bound, a.fmt, TR, s);
     else if (g.s2_short) launch_s2_short(p2, t2.mt_bound, a.fmt, s);
     else launch_s2_stream(p2, t2.mt_bound, a.fmt, s);
@@ -277,6 +295,7 @@ hipError_t launch_grouped_gemm(const GemmArgs& a, int stages, hipStream_t s, int
   const GemmWorkspace w = gemm_workspace(a.T, a.H, a.I, a.NE, a.k_total, a.fmt);
   const Geometry g = geometry(a);
   *variant = a.fmt == kFmtBf16 ? (g.s1_tiled ? 3 : 5)
+             : g.s1_block || g.s2_block ? 7
                                : (g.s2_tiled ? 2 : (g.s2_short ? 6 : (g.s1_tiled ? 4 : 1)));
   if (a.T == 0) return hipSuccess;
   if (a.fmt != 0 && a.fmt != 2 && a.fmt != 4 && a.fmt != kFmtBf16) return hipErrorNotSupported;

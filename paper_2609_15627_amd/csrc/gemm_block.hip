@@ -1,0 +1,422 @@
+// a5 / a6: grouped FP4 expert GEMMs, row-block geometry: between the
+// weight-streaming geometry (a few rows per expert) and the LDS-tiled one.
+//
+// From about ten rows per expert up to about sixty the stages are still bound
+// by the weight stream, but 16-row tiles read an expert's weights once per 16
+// rows, and their activation operands, loaded straight to registers, put each
+// of a load's lanes on another cache line (64 clocks of address work per KiB
+// against 16 for a weight load). Here a workgroup of four waves owns a tile of
+// 64 rows x 256 weight rows: every wave streams its own 64 weight rows (block
+// layout, one contiguous KiB per load, straight to registers) and multiplies
+// them with all rows of the tile, which the four waves stage in LDS together,
+// 128 bytes of a row to eight neighbouring lanes. The LDS-tiled geometry moves
+// the weights through LDS too, where two or three ring stages are all that
+// fit; four register buffers keep three K steps of weights in flight per wave.
+// Measured (MXFP8, H = 4096, I = 2048, 256 + 1 experts, top-8; layer us,
+// streaming / LDS-tiled / this): 333 tokens 643 / 809 / 633; 500: 794 / 824 / 650;
+// 1100: 1346 / 886 / 789; 1500: 1682 / 927 / 900; 2000: - / 967 / 990. At 1100
+// tokens stage 1 takes 475 us (4.8 TB/s of weights; 370 at the stream's own rate:
+// the epilogue and the first loads' chain through the sorted rows take 23 each).
+// K steps of 128: while step c is multiplied, the weights and activations of
+// step c + 3 are on their way; the activations of step c + 1 (loaded two steps
+// earlier) go to the other of two LDS slots at the end of the step, and one
+// barrier per step makes them visible. All loads are ordinary ones that the
+// compiler counts exactly (no DMA in the loop); activation loads go out before
+// the weight loads of the same step, so waiting for them leaves the younger
+// weights in flight. 16-row blocks past the tile's last row are not multiplied.
+#include "gemm_common.h"
+#include "gemm_launch.h"
+
+namespace moe {
+
+constexpr int RB = 4;  // 16-row blocks per tile
+
+template <int FA>
+struct BlkGeom {
+  static constexpr int kRow = FA == 4 ? 64 : 128;  // activation bytes per row per step
+  static constexpr int kLanes = kRow / 16;         // lanes per row of an activation load
+  static constexpr int kRows = 16 * RB;
+  static constexpr int kSlot = kRows * kRow;
+  static constexpr int kPerLoad = 64 / kLanes;     // rows per load instruction
+  static constexpr int kLoads = kRows / (4 * kPerLoad);  // loads per wave per step
+};
+
+// LDS byte of 16-byte chunk c of row r in a slot (spread over the banks).
+template <int FA>
+__device__ __forceinline__ int blk_chunk(int r, int c) {
+  return FA == 4 ? r * 64 + 16 * (c ^ ((r >> 2) & 3)) : r * 128 + 16 * (c ^ ((r >> 1) & 7));
+}
+
+// One wave's weights of a K step: 4 blocks of 16 rows, 128 elements.
+struct BlkW {
+  v4u b[4];
+};
+
+// Scale bytes of a row in LDS: pieces of 16 bytes (four K steps x four 32-element
+// blocks) with the two transposed, so that the dword of lane group g holds the
+// scales of its block for the piece's four steps and the product of step j picks
+// byte j. Rows are kb + 16 bytes apart (kb + 24 for K = 256): the 16 rows of an
+// operand block fall into different banks (at kb = 128 bytes apart eight of them
+// shared one, and a byte read per row and step took a fifth of stage 1).
+__host__ __device__ inline int blk_scale_stride(int kb) { return (kb + 15) / 16 * 16 + 16; }
+
+__device__ __forceinline__ v4u blk_transpose(v4u v) {
+  // bytes 4 j + g -> 4 g + j
+  const uint32_t t0 = __builtin_amdgcn_perm(v.y, v.x, 0x05010400);  // x0 y0 x1 y1
+  const uint32_t t1 = __builtin_amdgcn_perm(v.y, v.x, 0x07030602);  // x2 y2 x3 y3
+  const uint32_t t2 = __builtin_amdgcn_perm(v.w, v.z, 0x05010400);  // z0 w0 z1 w1
+  const uint32_t t3 = __builtin_amdgcn_perm(v.w, v.z, 0x07030602);
+  return v4u{__builtin_amdgcn_perm(t2, t0, 0x05040100), __builtin_amdgcn_perm(t2, t0, 0x07060302),
+             __builtin_amdgcn_perm(t3, t1, 0x05040100), __builtin_amdgcn_perm(t3, t1, 0x07060302)};
+}
+
+// Scale rows row(0) .. row(nr - 1) (kb bytes each) into LDS at dst, by `nth`
+// threads of which this is number t.
+template <typename RowFn>
+__device__ __forceinline__ void blk_scales(uint8_t* dst, RowFn row, int nr, int kb, int t, int nth) {
+  const int st = blk_scale_stride(kb);
+  if (kb % 16 == 0) {
+    const int pc = kb / 16;
+    for (int i = t; i < nr * pc; i += nth) {
+      const int r = i / pc, c = i % pc;
+      // scale rows are only 4-byte aligned
+      const uint32_t* q = reinterpret_cast<const uint32_t*>(row(r) + 16 * c);
+      *reinterpret_cast<v4u*>(dst + r * st + 16 * c) = blk_transpose(v4u{q[0], q[1], q[2], q[3]});
+    }
+  } else {  // K = 256: two steps
+    for (int r = t; r < nr; r += nth) {
+      const uint32_t* q = reinterpret_cast<const uint32_t*>(row(r));
+      *reinterpret_cast<v4u*>(dst + r * st) = blk_transpose(v4u{q[0], q[1], 0u, 0u});
+    }
+  }
+}
+
+// The K loop of a workgroup. arow(r): byte offset of tile row r's activations
+// from abase; wb[n]: weight block n (uniform) at K piece 0. NST: 0 for any multiple of 4 steps, else the exact (small) step count.
+// NRB: the tile's 16-row blocks that hold rows. The weights are the row operand,
+// so a lane's accumulator holds four consecutive weight rows of one activation
+// row. LDS: two activation slots, then the scale rows (blk_scales) of the 16 RB
+// activation rows and of the 4 x 64 weight rows; scales() stages them.
+template <int FA, int NRB, int NST, bool NT, typename RowFn, typename ScaleFn>
+__device__ __forceinline__ void blk_kloop_n(uint8_t* lds, const uint8_t* abase, RowFn arow,
+                                            const uint8_t* const* wb, int nst, int kb, int w,
+                                            int lane, v4f (*acc)[4], ScaleFn scales) {
+  using G = BlkGeom<FA>;
+  const int g = lane >> 4, c16 = lane & 15;
+  const uint32_t wo = 64 * c16 + 16 * g;  // this lane's bytes of a KiB of weights
+  uint32_t ao[G::kLoads];  // activation byte of this lane at step 0
+  int aw[G::kLoads];       // its LDS byte in a slot
+#pragma unroll
+  for (int i = 0; i < G::kLoads; ++i) {
+    const int r = G::kPerLoad * (G::kLoads * w + i) + lane / G::kLanes;
+    ao[i] = arow(r) + 16 * (lane % G::kLanes);
+    aw[i] = blk_chunk<FA>(r, lane % G::kLanes);
+  }
+  BlkW f[4];
+  v4u fa[4][G::kLoads];
+  auto load = [&](BlkW& q, v4u* a, int s) {
+    __builtin_amdgcn_sched_barrier(0);
+    const uint8_t* ab = abase + (size_t)s * G::kRow;
+#pragma unroll
+    for (int i = 0; i < G::kLoads; ++i) a[i] = ld16<false>(ab + ao[i]);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) q.b[n] = ld16<NT>(wb[n] + (size_t)s * 1024 + wo);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto put = [&](const v4u* a, int s) {
+#pragma unroll
+    for (int i = 0; i < G::kLoads; ++i)
+      *reinterpret_cast<v4u*>(lds + (s & 1) * G::kSlot + aw[i]) = a[i];
+  };
+  auto sync = [&]() {  // LDS only: the loads in flight stay in flight
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    asm volatile("s_barrier" ::: "memory");
+  };
+  const int st_ = blk_scale_stride(kb);
+  const uint8_t* const sa = lds + 2 * G::kSlot + c16 * st_ + 4 * g;
+  const uint8_t* const sb = lds + 2 * G::kSlot + (G::kRows + 64 * w + c16) * st_ + 4 * g;
+  // operand reads of row block 0 in slot 0
+  const int a0 = blk_chunk<FA>(c16, FA == 2 ? 2 * g : g);
+  const int a1 = FA == 4 ? 0 : blk_chunk<FA>(c16, FA == 2 ? 2 * g + 1 : 4 + g);
+  uint32_t as[NRB], bs[4];  // scales of four steps
+  auto group = [&](int s) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+      bs[n] = *reinterpret_cast<const uint32_t*>(sb + 16 * n * st_ + 4 * s);
+#pragma unroll
+    for (int m = 0; m < NRB; ++m)
+      as[m] = *reinterpret_cast<const uint32_t*>(sa + 16 * m * st_ + 4 * s);
+  };
+  auto mma = [&](auto J, const BlkW& q, int s) {
+    constexpr int j = decltype(J)::value;
+    const uint8_t* st = lds + (s & 1) * G::kSlot;
+    auto read = [&](int m) {
+      const v4u lo = *reinterpret_cast<const v4u*>(st + a0 + m * 16 * G::kRow);
+      if constexpr (FA == 4) {
+        return v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, 0, 0, 0, 0};
+      } else {
+        const v4u hi = *reinterpret_cast<const v4u*>(st + a1 + m * 16 * G::kRow);
+        return FA == 0 ? v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w,
+                             (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w}
+                       : v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, 0, 0};
+      }
+    };
+    v8i a[2];  // operands of the next two row blocks
+    a[0] = read(0);
+    if constexpr (NRB > 1) a[1] = read(1);
+#pragma unroll
+    for (int m = 0; m < NRB; ++m) {
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        const v4u bq = q.b[n];
+        const v8i b = v8i{(int)bq.x, (int)bq.y, (int)bq.z, (int)bq.w, 0, 0, 0, 0};
+        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+            b, a[m & 1], acc[m][n], 4, FA, j, (int)bs[n], j, (int)as[m]);
+      }
+      if (m + 2 < NRB) {
+        __builtin_amdgcn_sched_barrier(0);
+        a[m & 1] = read(m + 2);
+      }
+    }
+  };
+#pragma unroll
+  for (int m = 0; m < NRB; ++m)
+#pragma unroll
+    for (int n = 0; n < 4; ++n) acc[m][n] = v4f{0.f, 0.f, 0.f, 0.f};
+  constexpr int kFirst = NST > 0 && NST < 3 ? NST : 3;
+#pragma unroll
+  for (int s = 0; s < kFirst; ++s) load(f[s], fa[s], s);
+  scales();
+  put(fa[0], 0);
+  sync();
+  // step s = 4 i + J; last: the last four (or NST) steps, which load no more
+  // than exist
+  auto step = [&](auto J, int s, auto last, auto left) {
+    constexpr int j = decltype(J)::value;
+    constexpr int kLeft = decltype(left)::value;  // steps from this group's first to the end
+    constexpr bool kMore = !decltype(last)::value || j + 3 < kLeft;
+    constexpr bool kNext = !decltype(last)::value || j + 1 < kLeft;
+    if constexpr (kMore) load(f[(j + 3) & 3], fa[(j + 3) & 3], s + 3);
+    if constexpr (j == 0) group(s);
+    mma(J, f[j], s);
+    if constexpr (kNext) {
+      put(fa[(j + 1) & 3], s + 1);
+      sync();
+    }
+  };
+  using std::integral_constant;
+  if constexpr (NST > 0) {
+    static_for<NST>([&](auto J) {
+      step(J, decltype(J)::value, integral_constant<bool, true>{}, integral_constant<int, NST>{});
+    });
+  } else {
+    int s = 0;
+    for (; s + 4 < nst; s += 4)
+      static_for<4>([&](auto J) {
+        step(J, s + decltype(J)::value, integral_constant<bool, false>{},
+             integral_constant<int, 4>{});
+      });
+    static_for<4>([&](auto J) {
+      step(J, s + decltype(J)::value, integral_constant<bool, true>{},
+           integral_constant<int, 4>{});
+    });
+  }
+}
+
+// ntiles: the expert's row tiles. Weights that one tile alone reads carry the
+// streaming (non-temporal) policy; where several tiles of an expert read them, on
+// one XCD at about the same time, they are kept in its L2 (at 62 rows per
+// expert, two fifths of the experts with a second tile: layer 1060 us with the
+// streaming policy for all, 996 with none; at 17 rows 650 and 688).
+template <int FA, int NST, typename RowFn, typename ScaleFn>
+__device__ __forceinline__ void blk_kloop(uint8_t* lds, const uint8_t* abase, RowFn arow,
+                                          const uint8_t* const* wb, int nst, int kb, int w,
+                                          int lane, int nrb, int ntiles, v4f (*acc)[4],
+                                          ScaleFn scales) {
+#define MOE_BLK(N)                                                                               \
+  (ntiles == 1                                                                                   \
+       ? blk_kloop_n<FA, N, NST, true>(lds, abase, arow, wb, nst, kb, w, lane, acc, scales) \
+       : blk_kloop_n<FA, N, NST, false>(lds, abase, arow, wb, nst, kb, w, lane, acc, scales))
+  if (nrb == 4) return MOE_BLK(4);
+  if (nrb == 3) return MOE_BLK(3);
+  if (nrb == 2) return MOE_BLK(2);
+  MOE_BLK(1);
+#undef MOE_BLK
+}
+
+// SwiGLU and per-32 quantisation of one 16-row block of h: a lane holds
+// columns 16 n + 4 g + q (n, q: block and element) of row c16; gate blocks acc[0],
+// acc[1], up blocks acc[2], acc[3]; a row's 32 values sit in its four lane groups.
+template <int FA>
+__device__ __forceinline__ void blk_swiglu(const v4f* acc, const S1Args& p, int row0, int nrows,
+                                           int hc0, int g, int c16) {
+  float h[2][4];
+  float m = 0.0f;
+#pragma unroll
+  for (int n = 0; n < 2; ++n)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float G = acc[n][q], U = acc[n + 2][q];
+      h[n][q] = G * U / (1.0f + expf(-G));
+      m = fmaxf(m, fabsf(h[n][q]));
+    }
+  m = fmaxf(m, __int_as_float(wave_partner<4>(__float_as_int(m))));
+  m = fmaxf(m, __int_as_float(wave_partner<5>(__float_as_int(m))));
+  const int X = mx_scale_exp<FA>(m);
+  if (c16 >= nrows) return;
+  const size_t r = (size_t)row0 + c16;
+  uint8_t* dst = p.hq + (r * (p.I / 32) + hc0 / 32) * ActBytes<FA>::kBlock;
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+    if constexpr (FA == 0) {
+      *reinterpret_cast<uint32_t*>(dst + 16 * n + 4 * g) =
+          e4m3_pack4(ldexpf(h[n][0], -X), ldexpf(h[n][1], -X), ldexpf(h[n][2], -X),
+                     ldexpf(h[n][3], -X));
+    } else {
+      uint32_t v = 0;
+      constexpr int kB = Elem<FA>::kBits;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v |= mx_encode<FA>(ldexpf(h[n][q], -X)) << (kB * q);
+      if constexpr (FA == 4) {
+        *reinterpret_cast<uint16_t*>(dst + 8 * n + 2 * g) = (uint16_t)v;
+      } else {  // four codes at 6 bits: three bytes of the slot
+#pragma unroll
+        for (int q = 0; q < 3; ++q) dst[12 * n + 3 * g + q] = (uint8_t)(v >> (8 * q));
+      }
+    }
+  }
+  if (g == 0) p.hs[r * (p.I / 32) + hc0 / 32] = (uint8_t)(X + 127);
+}
+
+// Stage 1: 128 h columns per workgroup; wave w streams the gate rows and the
+// matching up rows of 32 of them, so SwiGLU and the per-32 quantisation of h
+// run in registers.
+template <int FA, int NST>
+__global__ __launch_bounds__(256, 2) void s1_block_kernel(S1Args p) {
+  using G = BlkGeom<FA>;
+  constexpr int kAB = ActBytes<FA>::kBlock;
+  int4 tile;
+  int nt;
+  if (!tile_of_block(p.t, &tile, &nt)) return;
+  const int e = tile.x, row0 = tile.y, nrows = tile.z;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+  const int kb = p.H / 32;
+  const int hc0 = nt * 128 + 32 * w;  // first h column of the wave
+  const size_t ebase = (size_t)e * 2 * p.I;
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const uint8_t* wb[4];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    const size_t r = ebase + hc0 + 16 * (n & 1) + (n < 2 ? 0 : p.I);
+    wb[n] = p.w13 + r * (p.H / 2);
+  }
+  auto token = [&](int r) { return p.sorted[row0 + (r < nrows ? r : 0)] / p.k_total; };
+  v4f acc[RB][4];
+  const int nrb = (nrows + 15) / 16;
+  blk_kloop<FA, NST>(
+      lds, p.xq, [&](int r) { return (uint32_t)token(r) * (uint32_t)(kb * kAB); }, wb, kb / 4, kb,
+      w, lane, nrb, tile.w, acc, [&]() {
+        uint8_t* sl = lds + 2 * G::kSlot;
+        const int st = blk_scale_stride(kb);
+        blk_scales(sl, [&](int r) { return p.xs + (size_t)token(r) * kb; }, 16 * nrb, kb,
+                   threadIdx.x, 256);
+        blk_scales(sl + (G::kRows + 64 * w) * st,
+                   [&](int r) {
+                     return p.w13s + (ebase + hc0 + (r < 32 ? r : p.I + r - 32)) * kb;
+                   },
+                   64, kb, lane, 64);
+      });
+#pragma unroll
+  for (int m = 0; m < RB; ++m) {
+    if (m >= nrb) break;
+    blk_swiglu<FA>(acc[m], p, row0 + 16 * m, nrows - 16 * m, hc0, g, c16);
+  }
+}
+
+// Stage 2: 256 output columns per workgroup, 64 per wave.
+template <int FA, int NST>
+__global__ __launch_bounds__(256, 2) void s2_block_kernel(S2Args p) {
+  using G = BlkGeom<FA>;
+  constexpr int kAB = ActBytes<FA>::kBlock;
+  int4 tile;
+  int nt;
+  if (!tile_of_block(p.t, &tile, &nt)) return;
+  const int e = tile.x, row0 = tile.y, nrows = tile.z;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+  const int kb = p.I / 32;
+  const int nc0 = nt * 256 + 64 * w;  // first output column of the wave
+  const size_t rbase = (size_t)e * p.H + nc0;
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const uint8_t* wb[4];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) wb[n] = p.w2 + (rbase + 16 * n) * (p.I / 2);
+  v4f acc[RB][4];
+  const int nrb = (nrows + 15) / 16;
+  const uint8_t* abase = p.hq + (size_t)row0 * (kb * kAB);
+  blk_kloop<FA, NST>(
+      lds, abase, [&](int r) { return (uint32_t)(r < nrows ? r : 0) * (uint32_t)(kb * kAB); }, wb,
+      kb / 4, kb, w, lane, nrb, tile.w, acc, [&]() {
+        uint8_t* sl = lds + 2 * G::kSlot;
+        const int st = blk_scale_stride(kb);
+        blk_scales(sl, [&](int r) { return p.hs + ((size_t)row0 + (r < nrows ? r : 0)) * kb; },
+                   16 * nrb, kb, threadIdx.x, 256);
+        blk_scales(sl + (G::kRows + 64 * w) * st, [&](int r) { return p.w2s + (rbase + r) * kb; },
+                   64, kb, lane, 64);
+      });
+#pragma unroll
+  for (int m = 0; m < RB; ++m) {
+    if (m >= nrb) break;
+    if (16 * m + c16 < nrows) {
+      float* dst = p.partials + (size_t)p.sorted[row0 + 16 * m + c16] * p.H + nc0 + 4 * g;
+#pragma unroll
+      for (int n = 0; n < 4; ++n) *reinterpret_cast<v4f*>(dst + 16 * n) = acc[m][n];
+    }
+  }
+}
+
+int block_rows() { return 16 * RB; }
+
+size_t block_lds_bytes(int fa, int K) {
+  return (size_t)2 * 16 * RB * (fa == 4 ? 64 : 128) +
+         (size_t)(16 * RB + 256) * blk_scale_stride(K / 32);
+}
+
+bool block_k_ok(int K) { return K == 256 || K % 512 == 0; }
+
+template <typename KD, typename K2, typename P>
+static void launch_block(KD kd, K2 k2, const P& p0, int K, int ntl, long mt, int fa, hipStream_t s) {
+  P q = p0;
+  q.t.n_ntiles = ntl;
+  q.t.ngroup = n_group_of(ntl);
+  const long n = mt * ntl;
+  const dim3 grid((int)((n + 7) / 8 * 8)), block(256);
+  const size_t lds = block_lds_bytes(fa, K);
+  if (K == 256) hipLaunchKernelGGL(k2, grid, block, lds, s, q);
+  else hipLaunchKernelGGL(kd, grid, block, lds, s, q);
+}
+
+template <int FA>
+static void launch_b1(const S1Args& p, long mt, hipStream_t s) {
+  launch_block(s1_block_kernel<FA, 0>, s1_block_kernel<FA, 2>, p, p.H, p.I / 128, mt, FA, s);
+}
+
+template <int FA>
+static void launch_b2(const S2Args& p, long mt, hipStream_t s) {
+  launch_block(s2_block_kernel<FA, 0>, s2_block_kernel<FA, 2>, p, p.I, p.H / 256, mt, FA, s);
+}
+
+void launch_s1_block(const S1Args& p, long mt, int fa, hipStream_t s) {
+  if (fa == 0) launch_b1<0>(p, mt, s);
+  else if (fa == 2) launch_b1<2>(p, mt, s);
+  else launch_b1<4>(p, mt, s);
+}
+
+void launch_s2_block(const S2Args& p, long mt, int fa, hipStream_t s) {
+  if (fa == 0) launch_b2<0>(p, mt, s);
+  else if (fa == 2) launch_b2<2>(p, mt, s);
+  else launch_b2<4>(p, mt, s);
+}
+
+}  // namespace moe

@@ -100,7 +100,7 @@ __device__ __forceinline__ uint32_t gather_scales(const uint8_t* p, int g) {
 constexpr int kQueueInts = 16;  // ints of the persistent geometry's work queue
 
 struct TileArgs {
-  const int4* tiles;    // (expert, first sorted row, rows, 0)
+  const int4* tiles;    // (expert, first sorted row, rows, row tiles of the expert)
   const int* ntiles;    // number of valid tiles
   int mt_bound;         // tiles the grid was sized for
   int n_ntiles;         // N tiles per expert

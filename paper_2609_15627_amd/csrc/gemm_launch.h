@@ -40,6 +40,15 @@ bool tiled_k_ok(int K);       // a K extent fits the tiled K loop
 void launch_s1_tiled(const S1Args& p, long mt, int fa, int rows, hipStream_t s);
 void launch_s2_tiled(const S2Args& p, long mt, int fa, int rows, hipStream_t s);
 
+// Row-block geometry (between streaming and tiled): tiles of block_rows()
+// rows, weights streamed to registers, activations staged in LDS. Stage 1
+// takes K = H, stage 2 K = I and H % 256 == 0.
+int block_rows();
+bool block_k_ok(int K);
+size_t block_lds_bytes(int fa, int K);
+void launch_s1_block(const S1Args& p, long mt, int fa, hipStream_t s);
+void launch_s2_block(const S2Args& p, long mt, int fa, hipStream_t s);
+
 // Short-K geometry of stage 2 (K = I of 128 or 256, many rows per expert):
 // row tiles of short_rows() rows, the whole K extent of a tile in LDS.
 int short_rows();

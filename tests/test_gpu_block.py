@@ -1,0 +1,58 @@
+"""The row-block geometry (64-row tiles, weights streamed to registers) against
+the oracle, at the edges of its tiles, K loops and dispatch rule."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from tests import gpu_common as gc
+from tests.gpu_common import log
+from tests.test_gpu_layer import assert_repeats_identical, check_against_oracle, run_layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def m():
+    from paper_2609_15627_amd import moe
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return moe
+
+
+@pytest.mark.parametrize("fmt", ["e4m3", "e2m3", "e2m1"])
+@pytest.mark.parametrize("T,H,I,E,k,S,routing", [
+    (410, 512, 2048, 24, 2, 0, "normal"),    # ~34 rows: one tile per expert, K = 512 and 2048
+    (280, 1024, 2048, 32, 4, 1, "zipf"),     # empty experts, one row, several tiles; shared expert
+    (430, 256, 2048, 16, 2, 0, "normal"),    # K = 256 (two steps) in stage 1, one N tile in stage 2
+    (700, 512, 256, 64, 4, 0, "normal"),     # K = 256 in stage 2
+    (230, 768, 2048, 72, 4, 0, "normal"),    # stage 1 streams (H = 768)
+    (500, 512, 384, 60, 6, 1, "normal"),     # stage 2 streams (I = 384)
+])
+def test_block_layers(m, T, H, I, E, k, S, routing, fmt):
+    cfg = synth.LayerConfig("block", T, H, E, k, I, S, routing, 7 + T, zipf_empty=3)
+    inp = synth.make_inputs(cfg)
+    log(f"row-block layer {(T, H, I, E, k, S, routing)} {fmt}")
+    w = gc.dev_expert_weights(inp.weights)
+    x = gc.to_dev_bf16(inp.x)
+    assert not m.moe_fp4_grouped_gemm_combine_supported(T, H, I, cfg.NE, cfg.k_total, fmt)
+    layer, out = run_layer(m, cfg, x, w, logits=inp.logits, fmt=fmt)
+    assert m.moe_last_variant() == m.VARIANT_BLOCK
+    check_against_oracle(cfg, inp, layer, out, np.arange(cfg.T), fmt)
+    counts = np.diff(layer.perm[1].cpu().numpy())
+    log(f"  rows per expert {counts.min()}..{counts.max()}")
+    assert_repeats_identical(layer, x, w, out, logits=inp.logits, reps=3)
+
+
+def test_block_rule_keeps_the_fused_shapes_streaming(m):
+    """Where the fused down + combine is available the two calls stream, with its
+    bits, whatever the rows per expert."""
+    cfg = synth.LayerConfig("few", 380, 512, 16, 2, 2048, 0, "normal", 3)
+    assert m.moe_fp4_grouped_gemm_combine_supported(380, 512, 2048, 16, 2)
+    inp = synth.make_inputs(cfg)
+    log("row-block rule")
+    w = gc.dev_expert_weights(inp.weights)
+    _, a = run_layer(m, cfg, gc.to_dev_bf16(inp.x), w, logits=inp.logits, fused=False)
+    assert m.moe_last_variant() == m.VARIANT_STREAM
+    a = a.clone()
+    _, b = run_layer(m, cfg, gc.to_dev_bf16(inp.x), w, logits=inp.logits, fused=True)
+    assert np.array_equal(gc.bf16_bits(a), gc.bf16_bits(b))
