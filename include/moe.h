@@ -387,6 +387,36 @@ moe_status moe_fp4_grouped_gemm_combine(const uint16_t* x, int T, int H, int I,
 moe_status moe_combine_fixed_order(const float* partials, const float* topk_w, int T, int H,
                                    int k_total, uint16_t* out, void* stream);
 
+/* ---- the whole layer ---------------------------------------------------------
+ * One forward (the call sequence at the top of this file) as one call, with the
+ * same results in every buffer: moe_router_logits (with w_router, into
+ * logits_buf), moe_route_topk, moe_permute, moe_fp4_grouped_gemm and
+ * moe_combine_fixed_order, or with fused set
+ * moe_fp4_grouped_gemm_combine. Every check runs before anything is enqueued.
+ * Small batches (T * (k + n_shared) <= 1024, n_experts_total <= 512, not the
+ * LDS-tiled geometry) sort, build the tile lists and quantise x in one launch,
+ * up to 16 tokens with the routing. */
+typedef struct {
+  int T, H, E, k, n_shared, I, n_experts_total; /* E: columns of the logits */
+  moe_act_format f;
+  int fused;                /* nonzero: down projection fused with the combine */
+  const uint16_t* x;        /* [T, H] */
+  const float* logits;      /* [T, E]; ignored with w_router */
+  const uint16_t* w_router; /* [E, H] or NULL */
+  float* logits_buf;        /* [T, E], written with w_router */
+  const uint8_t *w13, *w13_s, *w2, *w2_s;
+  int32_t* topk_ids;        /* [T, k + n_shared] */
+  float* topk_w;            /* [T, k + n_shared] */
+  int32_t *counts, *offsets, *sorted, *pos;
+  void* perm_ws;
+  size_t perm_ws_bytes;
+  void* gemm_ws;
+  size_t gemm_ws_bytes;
+  float* partials;          /* [T * (k + n_shared), H] (unused when fused) */
+  uint16_t* out;            /* [T, H] */
+} moe_layer_args;
+moe_status moe_layer_forward(const moe_layer_args* args, void* stream);
+
 /* ---- diagnostics ------------------------------------------------------------ */
 
 /* Human-readable name of a status code (static storage). */

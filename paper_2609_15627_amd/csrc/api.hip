@@ -87,21 +87,35 @@ moe_status moe_set_tiled_rows(int rows) {
   return MOE_OK;
 }
 
-moe_status moe_router_logits(const uint16_t* x, const uint16_t* w_router, int T, int H, int E,
-                             float* logits, void* stream) {
+static moe_status check_router_logits(const uint16_t* x, const uint16_t* w_router, int T, int H,
+                                      int E, const float* logits) {
   if (T < 0 || H <= 0 || H % 8 || E < 1 || E > MOE_MAX_EXPERTS) return MOE_ERR_INVALID_ARG;
   if ((long)T * E >= (1L << 31) / 64) return MOE_ERR_INVALID_ARG;
   if (T > 0 && (!x || !w_router || !logits)) return MOE_ERR_INVALID_ARG;
   if (!aligned(x, 16) || !aligned(w_router, 16)) return MOE_ERR_INVALID_ARG;
+  return MOE_OK;
+}
+
+moe_status moe_router_logits(const uint16_t* x, const uint16_t* w_router, int T, int H, int E,
+                             float* logits, void* stream) {
+  const moe_status st = check_router_logits(x, w_router, T, H, E, logits);
+  if (st != MOE_OK) return st;
   return launched(moe::launch_router_logits(x, w_router, T, H, E, logits, as_stream(stream)));
 }
 
-moe_status moe_route_topk(const float* logits, int T, int E, int k, int n_shared, int32_t* topk_ids,
-                          float* topk_w, void* stream) {
+static moe_status check_route_topk(const float* logits, int T, int E, int k, int n_shared,
+                                   const int32_t* topk_ids, const float* topk_w) {
   if (T < 0 || E < 1 || E > MOE_MAX_EXPERTS || k < 1 || k > E) return MOE_ERR_INVALID_ARG;
   if (n_shared != 0 && n_shared != 1) return MOE_ERR_INVALID_ARG;
   if (k + n_shared > MOE_MAX_K_TOTAL || !tokens_ok(T, k + n_shared)) return MOE_ERR_INVALID_ARG;
   if (T > 0 && (!logits || !topk_ids || !topk_w)) return MOE_ERR_INVALID_ARG;
+  return MOE_OK;
+}
+
+moe_status moe_route_topk(const float* logits, int T, int E, int k, int n_shared, int32_t* topk_ids,
+                          float* topk_w, void* stream) {
+  const moe_status st = check_route_topk(logits, T, E, k, n_shared, topk_ids, topk_w);
+  if (st != MOE_OK) return st;
   return launched(moe::launch_route_topk(logits, T, E, k, n_shared, topk_ids, topk_w,
                                          as_stream(stream)));
 }
@@ -162,9 +176,10 @@ size_t moe_permute_workspace_bytes(int T, int n_experts_total, int k_total) {
   return moe::permute_workspace_bytes(T, n_experts_total, k_total);
 }
 
-moe_status moe_permute(const int32_t* topk_ids, int T, int n_experts_total, int k_total,
-                       int32_t* counts, int32_t* offsets, int32_t* sorted, int32_t* pos, void* ws,
-                       size_t ws_bytes, void* stream) {
+static moe_status check_permute(const int32_t* topk_ids, int T, int n_experts_total, int k_total,
+                                const int32_t* counts, const int32_t* offsets,
+                                const int32_t* sorted, const int32_t* pos, const void* ws,
+                                size_t ws_bytes) {
   if (T < 0 || n_experts_total < 1 || n_experts_total > MOE_MAX_EXPERTS_TOTAL) return MOE_ERR_INVALID_ARG;
   if (k_total < 1 || k_total > MOE_MAX_K_TOTAL || !tokens_ok(T, k_total)) return MOE_ERR_INVALID_ARG;
   if (!counts || !offsets) return MOE_ERR_INVALID_ARG;
@@ -172,6 +187,15 @@ moe_status moe_permute(const int32_t* topk_ids, int T, int n_experts_total, int 
   const size_t need = moe::permute_workspace_bytes(T, n_experts_total, k_total);
   if ((long)T * k_total > 1024 && (!ws || ws_bytes < need || !aligned(ws, 256)))
     return MOE_ERR_WORKSPACE;
+  return MOE_OK;
+}
+
+moe_status moe_permute(const int32_t* topk_ids, int T, int n_experts_total, int k_total,
+                       int32_t* counts, int32_t* offsets, int32_t* sorted, int32_t* pos, void* ws,
+                       size_t ws_bytes, void* stream) {
+  const moe_status st = check_permute(topk_ids, T, n_experts_total, k_total, counts, offsets,
+                                      sorted, pos, ws, ws_bytes);
+  if (st != MOE_OK) return st;
   return launched(moe::launch_permute(topk_ids, T, n_experts_total, k_total, counts, offsets, sorted,
                                       pos, ws, as_stream(stream)));
 }
@@ -229,13 +253,12 @@ moe_status moe_fp4_grouped_gemm_workspace_layout(int T, int H, int I, int n_expe
 // fused: stage 2 writes out through the combine (topk_w, out) instead of
 // partials. use_scratch: the workspace is the library's static scratch array
 // (ws is ignored); shapes that need more return MOE_ERR_WORKSPACE.
-static moe_status grouped_gemm(const uint16_t* x, int T, int H, int I, int n_experts_total,
-                               int k_total, const int32_t* offsets, const int32_t* sorted,
-                               const uint8_t* w13, const uint8_t* w13_s, const uint8_t* w2,
-                               const uint8_t* w2_s, moe_act_format f, float* partials,
-                               bool fused, const float* topk_w, uint16_t* out, void* ws,
-                               size_t ws_bytes, int stages, void* stream,
-                               bool use_scratch = false) {
+static moe_status check_gemm(const uint16_t* x, int T, int H, int I, int n_experts_total,
+                             int k_total, const int32_t* offsets, const int32_t* sorted,
+                             const uint8_t* w13, const uint8_t* w13_s, const uint8_t* w2,
+                             const uint8_t* w2_s, moe_act_format f, float* partials, bool fused,
+                             const float* topk_w, uint16_t* out, void* ws, size_t ws_bytes,
+                             int stages, bool use_scratch, moe::GemmArgs* args) {
   const int fc = fmt_code(f);
   if (fc < 0 || !gemm_dims_ok(T, H, I, n_experts_total, k_total)) return MOE_ERR_INVALID_ARG;
   if (stages < 1 || stages > 7) return MOE_ERR_INVALID_ARG;
@@ -255,13 +278,31 @@ static moe_status grouped_gemm(const uint16_t* x, int T, int H, int I, int n_exp
     if (T > 0 && scratch_address(&ws) != hipSuccess) return MOE_ERR_LAUNCH;
   }
   if (T > 0 && (!ws || ws_bytes < need || !aligned(ws, 256))) return MOE_ERR_WORKSPACE;
-  moe::GemmArgs a{x, T, H, I, n_experts_total, k_total, fc, offsets, sorted,
-                  w13, w13_s, w2, w2_s, partials, static_cast<uint8_t*>(ws), topk_w, out};
-  if (fused && T > 0 && !moe::fused_combine_ok(a)) return MOE_ERR_UNSUPPORTED;
+  *args = moe::GemmArgs{x, T, H, I, n_experts_total, k_total, fc, offsets, sorted,
+                        w13, w13_s, w2, w2_s, partials, static_cast<uint8_t*>(ws), topk_w, out};
+  if (fused && T > 0 && !moe::fused_combine_ok(*args)) return MOE_ERR_UNSUPPORTED;
+  return MOE_OK;
+}
+
+static moe_status run_gemm(const moe::GemmArgs& a, int stages, void* stream) {
   int variant = MOE_VARIANT_NONE;
   const moe_status st = launched(moe::launch_grouped_gemm(a, stages, as_stream(stream), &variant));
   g_last_variant = variant;
   return st;
+}
+
+static moe_status grouped_gemm(const uint16_t* x, int T, int H, int I, int n_experts_total,
+                               int k_total, const int32_t* offsets, const int32_t* sorted,
+                               const uint8_t* w13, const uint8_t* w13_s, const uint8_t* w2,
+                               const uint8_t* w2_s, moe_act_format f, float* partials,
+                               bool fused, const float* topk_w, uint16_t* out, void* ws,
+                               size_t ws_bytes, int stages, void* stream,
+                               bool use_scratch = false) {
+  moe::GemmArgs a;
+  const moe_status st =
+      check_gemm(x, T, H, I, n_experts_total, k_total, offsets, sorted, w13, w13_s, w2, w2_s, f,
+                 partials, fused, topk_w, out, ws, ws_bytes, stages, use_scratch, &a);
+  return st != MOE_OK ? st : run_gemm(a, stages, stream);
 }
 
 moe_status moe_fp4_grouped_gemm(const uint16_t* x, int T, int H, int I, int n_experts_total,
@@ -313,13 +354,67 @@ moe_status moe_fp4_grouped_gemm_combine(const uint16_t* x, int T, int H, int I,
                       f, nullptr, true, topk_w, out, ws, ws_bytes, stages, stream);
 }
 
-moe_status moe_combine_fixed_order(const float* partials, const float* topk_w, int T, int H,
-                                   int k_total, uint16_t* out, void* stream) {
+static moe_status check_combine(const float* partials, const float* topk_w, int T, int H,
+                                int k_total, const uint16_t* out) {
   if (T < 0 || H <= 0 || H % 8 || k_total < 1 || k_total > MOE_MAX_K_TOTAL || !tokens_ok(T, k_total))
     return MOE_ERR_INVALID_ARG;
   if (T > 0 && (!partials || !topk_w || !out)) return MOE_ERR_INVALID_ARG;
   if (!aligned(partials, 16) || !aligned(out, 16)) return MOE_ERR_INVALID_ARG;
+  return MOE_OK;
+}
+
+moe_status moe_combine_fixed_order(const float* partials, const float* topk_w, int T, int H,
+                                   int k_total, uint16_t* out, void* stream) {
+  const moe_status st = check_combine(partials, topk_w, T, H, k_total, out);
+  if (st != MOE_OK) return st;
   return launched(moe::launch_combine(partials, topk_w, T, H, k_total, out, as_stream(stream)));
+}
+
+moe_status moe_layer_forward(const moe_layer_args* a, void* stream) {
+  if (!a) return MOE_ERR_INVALID_ARG;
+  const int T = a->T, kt = a->k + a->n_shared;
+  const bool fused = a->fused != 0;
+  const float* logits = a->logits;
+  moe_status st = MOE_OK;
+  if (a->w_router) {
+    logits = a->logits_buf;
+    st = check_router_logits(a->x, a->w_router, T, a->H, a->E, logits);
+  }
+  if (st == MOE_OK) st = check_route_topk(logits, T, a->E, a->k, a->n_shared, a->topk_ids, a->topk_w);
+  if (st == MOE_OK)
+    st = check_permute(a->topk_ids, T, a->n_experts_total, kt, a->counts, a->offsets, a->sorted,
+                       a->pos, a->perm_ws, a->perm_ws_bytes);
+  moe::GemmArgs g;
+  if (st == MOE_OK)
+    st = check_gemm(a->x, T, a->H, a->I, a->n_experts_total, kt, a->offsets, a->sorted, a->w13,
+                    a->w13_s, a->w2, a->w2_s, a->f, fused ? nullptr : a->partials, fused, fused ? a->topk_w : nullptr,
+                    fused ? a->out : nullptr, a->gemm_ws, a->gemm_ws_bytes, 7, false, &g);
+  if (st == MOE_OK && !fused)
+    st = check_combine(a->partials, a->topk_w, T, a->H, kt, a->out);
+  if (st != MOE_OK) return st;
+
+  const hipStream_t s = as_stream(stream);
+  hipError_t e = hipSuccess;
+  if (a->w_router)
+    e = moe::launch_router_logits(a->x, a->w_router, T, a->H, a->E, a->logits_buf, s);
+  int stages = 7;
+  const bool front = moe::front_ok(g);
+  if (e == hipSuccess && !(front && moe::front_routes(T)))
+    e = moe::launch_route_topk(logits, T, a->E, a->k, a->n_shared, a->topk_ids, a->topk_w, s);
+  if (e != hipSuccess) return launched(e);
+  if (front) {
+    const moe::FrontIO io{moe::front_routes(T) ? logits : nullptr, a->E, a->k, a->n_shared,
+                          a->topk_ids, a->topk_w, a->counts, a->offsets, a->sorted, a->pos};
+    e = moe::launch_front_steps(g, io, s);
+    stages = 6;
+  } else {
+    e = moe::launch_permute(a->topk_ids, T, a->n_experts_total, kt, a->counts, a->offsets,
+                            a->sorted, a->pos, a->perm_ws, s);
+  }
+  if (e != hipSuccess) return launched(e);
+  st = run_gemm(g, stages, stream);
+  if (st != MOE_OK || fused) return st;
+  return launched(moe::launch_combine(a->partials, a->topk_w, T, a->H, kt, a->out, s));
 }
 
 moe_status moe_probe_scaled_mfma(const uint8_t* a, const uint8_t* sa, moe_act_format fa,

@@ -221,17 +221,51 @@ bool fused_combine_ok(const GemmArgs& a) {
          !g.s2_block && fused_lds_bytes(a.T, a.k_total, a.I) <= (size_t)max_lds_per_block();
 }
 
+// The row-tile lists of the two stages (stage 2 shares stage 1's when their
+// tiles have as many rows).
+struct Lists {
+  int TR;  // row tile of the LDS-tiled geometry
+  int BM1, BM2;
+  TileArgs t1, t2;
+};
+
+static Lists tile_lists(const GemmArgs& a, const GemmWorkspace& w, const Geometry& g) {
+  const bool bf = a.fmt == kFmtBf16;
+  const long A = (long)a.T * a.k_total;
+  Lists l;
+  l.TR = tiled_rows(A, a.NE);
+  l.BM1 = g.s1_block ? block_rows()
+                     : g.s1_tiled ? (bf ? bf16_rows() : l.TR) : (bf ? bf16_stream_rows() : 16);
+  l.BM2 = g.s2_block   ? block_rows()
+          : g.s2_tiled ? (bf ? bf16_rows() : l.TR)
+                       : (g.s2_short ? short_rows() : (bf ? bf16_stream_rows() : 16));
+  uint8_t* lists = a.ws + w.off[4];
+  l.t1 = tile_list(lists, A, a.NE, l.BM1);
+  l.t2 = l.BM2 == l.BM1 ? l.t1 : tile_list(lists + (w.off[5] - w.off[4]) / 2, A, a.NE, l.BM2);
+  return l;
+}
+
+bool front_ok(const GemmArgs& a) {
+  const Geometry g = geometry(a);
+  return front_sizes_ok(a.T, a.NE, a.k_total) && (a.fmt == kFmtBf16 || (!g.s1_tiled && !g.s2_tiled));
+}
+
+hipError_t launch_front_steps(const GemmArgs& a, const FrontIO& io, hipStream_t s) {
+  const GemmWorkspace w = gemm_workspace(a.T, a.H, a.I, a.NE, a.k_total, a.fmt);
+  const Lists l = tile_lists(a, w, geometry(a));
+  return launch_front(FrontArgs{a.x, a.fmt == kFmtBf16 ? 0 : (long)a.T * (a.H / 32),
+                                a.ws + w.off[0], a.ws + w.off[1], io.logits, a.T, io.E, io.k,
+                                io.n_shared, io.ids, io.w, a.NE, 0, a.fmt, io.counts, io.offsets,
+                                io.sorted, io.pos, l.BM1, l.BM2, l.t1, l.t2},
+                      s);
+}
+
 static hipError_t launch_geometry(const GemmArgs& a, const GemmWorkspace& w, int stages,
                                   Geometry g, hipStream_t s) {
   const bool bf = a.fmt == kFmtBf16;
-  const long A = (long)a.T * a.k_total;
-  const int TR = tiled_rows(A, a.NE);
-  const int BM1 = g.s1_block ? block_rows() : g.s1_tiled ? (bf ? bf16_rows() : TR) : (bf ? bf16_stream_rows() : 16);
-  const int BM2 = g.s2_block ? block_rows() : g.s2_tiled ? (bf ? bf16_rows() : TR)
-                             : (g.s2_short ? short_rows() : (bf ? bf16_stream_rows() : 16));
-  uint8_t* lists = a.ws + w.off[4];
-  const TileArgs t1 = tile_list(lists, A, a.NE, BM1);
-  const TileArgs t2 = BM2 == BM1 ? t1 : tile_list(lists + (w.off[5] - w.off[4]) / 2, A, a.NE, BM2);
+  const Lists l = tile_lists(a, w, g);
+  const int TR = l.TR, BM1 = l.BM1, BM2 = l.BM2;
+  const TileArgs &t1 = l.t1, &t2 = l.t2;
   if (stages & 1) {
     // quantisation of x (none under the BF16 contract) and the tile list(s)
     const long nblk = bf ? 0 : (long)a.T * (a.H / 32);

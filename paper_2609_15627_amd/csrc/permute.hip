@@ -18,12 +18,10 @@
 // Small inputs (one chunk) run all three steps in one workgroup, spread over
 // its 16 waves when the experts' per-wave counts fit LDS.
 // Integer counting only, so the result is exact and run-to-run identical.
-#include "moe_dev.h"
 #include "moe_launch.h"
+#include "permute_dev.h"
 
 namespace moe {
-
-constexpr int kChunk = 1024;
 
 __global__ __launch_bounds__(256) void perm_hist(const int32_t* __restrict__ ids, int A, int NE,
                                                  int32_t* __restrict__ hist) {
@@ -131,45 +129,6 @@ __global__ __launch_bounds__(64) void perm_scatter(const int32_t* __restrict__ i
   scatter_chunk(ids, base, min(A, base + kChunk), NE, nbits, cursor, sorted, pos);
 }
 
-// Wave-level part of the 16-wave placement: assignment a of this lane (a < A
-// taken), its expert e (ok: a valid id) and its rank among the wave's
-// earlier lanes with the same expert; the group's highest lane records the
-// group size in cnt[w * NE + e] (cnt zeroed beforehand, a barrier after).
-__device__ __forceinline__ void wave_rank16(const int32_t* __restrict__ ids, int a, int A, int NE,
-                                            int nbits, int32_t* cnt, int* e_out, bool* ok_out,
-                                            int* rank_out) {
-  const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int e = a < A ? ids[a] : -1;
-  const bool ok = (unsigned)e < (unsigned)NE;
-  uint64_t peers = __ballot(ok);
-  for (int b = 0; b < nbits; ++b) {
-    const bool bit = ok && ((e >> b) & 1);
-    const uint64_t m = __ballot(bit);
-    peers &= bit ? m : ~m;
-  }
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
-  const int rank = __popcll(peers & lt);
-  __syncthreads();  // cnt was zeroed by other threads
-  if (ok && (peers >> lane) == 1ull) cnt[w * NE + e] = rank + 1;
-  *e_out = e;
-  *ok_out = ok;
-  *rank_out = rank;
-}
-
-// Exclusive prefix of the 16 per-wave counts of expert threadIdx.x (in
-// place); returns the expert's total. Call after a barrier.
-__device__ __forceinline__ int prefix_waves16(int32_t* cnt, int NE) {
-  int c = 0;
-  if ((int)threadIdx.x < NE) {
-    for (int v = 0; v < 16; ++v) {
-      const int n = cnt[v * NE + threadIdx.x];
-      cnt[v * NE + threadIdx.x] = c;
-      c += n;
-    }
-  }
-  return c;
-}
-
 // The scatter with 16 waves per chunk (NE <= kSmallNE).
 __global__ __launch_bounds__(1024) void perm_scatter16(const int32_t* __restrict__ ids, int A,
                                                        int NE, int nbits,
@@ -243,7 +202,6 @@ __global__ __launch_bounds__(1024) void perm_small(const int32_t* __restrict__ i
 // per-wave count of every expert in LDS, and their exclusive prefix over the
 // waves give each assignment its slot with no serial pass (stable: wave w's
 // assignments precede wave w + 1's, lanes in order).
-constexpr int kSmallNE = 512;
 
 __global__ __launch_bounds__(1024) void perm_small16(const int32_t* __restrict__ ids, int A, int NE,
                                                      int nbits, int32_t* __restrict__ counts,
@@ -251,28 +209,8 @@ __global__ __launch_bounds__(1024) void perm_small16(const int32_t* __restrict__
                                                      int32_t* __restrict__ sorted,
                                                      int32_t* __restrict__ pos) {
   extern __shared__ int32_t sh[];
-  int32_t* cnt = sh;             // [16][NE]: per-wave counts, then their prefix over waves
-  int32_t* off = sh + 16 * NE;   // [NE]: expert offsets
-  for (int i = threadIdx.x; i < 16 * NE; i += blockDim.x) cnt[i] = 0;
-  int e, rank;
-  bool ok;
-  wave_rank16(ids, (int)threadIdx.x, A, NE, nbits, cnt, &e, &ok, &rank);
-  __syncthreads();
-  const int c = prefix_waves16(cnt, NE);
-  int total;
-  const int p0 = block_exclusive_scan_1024(c, &total);
-  if ((int)threadIdx.x < NE) {
-    counts[threadIdx.x] = c;
-    offsets[threadIdx.x] = p0;
-    off[threadIdx.x] = p0;
-  }
-  if (threadIdx.x == 0) offsets[NE] = total;
-  __syncthreads();
-  if (ok) {
-    const int dest = off[e] + cnt[(threadIdx.x / kWave) * NE + e] + rank;
-    sorted[dest] = threadIdx.x;
-    pos[threadIdx.x] = dest;
-  }
+  int c, off;
+  perm_place16(ids, A, NE, nbits, sh, counts, offsets, sorted, pos, &c, &off);
 }
 
 size_t permute_workspace_bytes(int T, int NE, int k_total) {

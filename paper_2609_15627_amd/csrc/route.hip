@@ -8,6 +8,7 @@
 // denominator summed in pick order.
 #include "gemm_common.h"
 #include "moe_launch.h"
+#include "route_dev.h"
 
 #include <type_traits>
 
@@ -302,7 +303,6 @@ __global__ __launch_bounds__(512) void router_logits_lds_kernel(const uint16_t* 
     }
 }
 
-// EPL = experts held per lane (ceil(E / 64) rounded up to a power of two).
 template <int EPL>
 __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict__ logits, int T,
                                                          int E, int k, int n_shared,
@@ -311,53 +311,9 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict
   const int t = (int)(((long)blockIdx.x * blockDim.x + threadIdx.x) / kWave);
   const int lane = threadIdx.x % kWave;
   if (t >= T) return;
-  const float* row = logits + (size_t)t * E;
-  float v[EPL];
-  bool live[EPL];
-#pragma unroll
-  for (int j = 0; j < EPL; ++j) {
-    const int e = lane + kWave * j;
-    live[j] = e < E;
-    float x = live[j] ? row[e] : -INFINITY;
-    v[j] = (x != x) ? -INFINITY : x;  // NaN reads as -inf
-  }
-  float my_val = 0.0f;
-  int my_id = 0;
-  for (int r = 0; r < k; ++r) {
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
-#pragma unroll
-    for (int j = 0; j < EPL; ++j) {
-      const int e = lane + kWave * j;
-      if (live[j] && (v[j] > bv || (v[j] == bv && e < bi))) {
-        bv = v[j];
-        bi = e;
-      }
-    }
-    wave_argmax(bv, bi);
-    // every lane now holds the same (bv, bi); retire the pick
-#pragma unroll
-    for (int j = 0; j < EPL; ++j)
-      if (lane + kWave * j == bi) live[j] = false;
-    if (lane == r) {
-      my_val = bv;
-      my_id = bi;
-    }
-  }
-  const float l0 = lane_value(my_val, 0);
-  const float ex = lane < k ? expf(my_val - l0) : 0.0f;
-  float den = 0.0f;
-  for (int j = 0; j < k; ++j) den += lane_value(ex, j);
   const int kt = k + n_shared;
-  int32_t* id_row = ids + (size_t)t * kt;
-  float* w_row = wts + (size_t)t * kt;
-  if (lane < k) {
-    id_row[lane] = my_id;
-    w_row[lane] = ex / den;
-  } else if (lane == k && n_shared) {
-    id_row[lane] = E;
-    w_row[lane] = 1.0f;
-  }
+  route_plain_token<EPL>(logits + (size_t)t * E, E, k, n_shared, ids + (size_t)t * kt,
+                         wts + (size_t)t * kt, lane);
 }
 
 // Routing variants. One wave per token, lane l holds experts l, l + 64, ...

@@ -50,6 +50,7 @@ _SIGNATURES = {
     "moe_fp4_grouped_gemm_combine": (_I, [_P, _I, _I, _I, _I, _I, _P, _P, _P, _P, _P, _P, _I, _P,
                                           _P, _P, _SZ, _I, _P]),
     "moe_combine_fixed_order": (_I, [_P, _P, _I, _I, _I, _P, _P]),
+    "moe_layer_forward": (_I, [_P, _P]),
     "moe_status_string": (ctypes.c_char_p, [_I]),
     "moe_last_variant": (_I, []),
     "moe_probe_scaled_mfma": (_I, [_P, _P, _I, _P, _P, _P, _P]),
@@ -392,6 +393,15 @@ def moe_probe_scaled_mfma(a, sa, b, sb, fmt="e4m3", d=None, stream=None):
     return d
 
 
+class _LayerArgs(ctypes.Structure):
+    _fields_ = [(n, _I) for n in ("T", "H", "E", "k", "n_shared", "I", "n_experts_total", "f",
+                                "fused")] + \
+        [(n, _P) for n in ("x", "logits", "w_router", "logits_buf", "w13", "w13_s", "w2", "w2_s",
+                           "topk_ids", "topk_w", "counts", "offsets", "sorted", "pos", "perm_ws")] + \
+        [("perm_ws_bytes", _SZ), ("gemm_ws", _P), ("gemm_ws_bytes", _SZ), ("partials", _P),
+         ("out", _P)]
+
+
 class MoELayer:
     """One routed-MoE layer forward through the four library calls.
 
@@ -440,8 +450,10 @@ class MoELayer:
         recorded between the steps (route, permute, quantise, gate/up, down,
         combine) for per-step timing; with the fused path "down" is the fused
         down projection + combine and "combine" is empty."""
+        if not events:
+            return self._forward(x, weights, logits, w_router, stream)
         w13, w13_s, w2, w2_s = weights
-        ev = (lambda i: events[i].record(stream)) if events else (lambda i: None)
+        ev = lambda i: events[i].record(stream)  # noqa: E731
         ev(0)
         if logits is None:
             logits = moe_router_logits(x, w_router, self.logits, stream=stream)
@@ -452,26 +464,59 @@ class MoELayer:
         ev(2)
         if self.fused:
             g = (x, offsets, srt, w13, w13_s, w2, w2_s, self.w, self.fmt)
-            if events:
-                for i, st in enumerate((1, 2, 4)):
-                    moe_fp4_grouped_gemm_combine(*g, out=self.out, ws=self.gemm_ws, stream=stream,
-                                                 stages=st)
-                    ev(3 + i)
-            else:
-                moe_fp4_grouped_gemm_combine(*g, out=self.out, ws=self.gemm_ws, stream=stream)
+            for i, st in enumerate((1, 2, 4)):
+                moe_fp4_grouped_gemm_combine(*g, out=self.out, ws=self.gemm_ws, stream=stream,
+                                             stages=st)
+                ev(3 + i)
             ev(6)
             return self.out
         g = (x, offsets, srt, w13, w13_s, w2, w2_s, self.kt, self.fmt)
-        if events:
-            for i, st in enumerate((1, 2, 4)):
-                moe_fp4_grouped_gemm(*g, partials=self.partials, ws=self.gemm_ws, stream=stream,
-                                     stages=st)
-                ev(3 + i)
-        else:
-            moe_fp4_grouped_gemm(*g, partials=self.partials, ws=self.gemm_ws, stream=stream)
+        for i, st in enumerate((1, 2, 4)):
+            moe_fp4_grouped_gemm(*g, partials=self.partials, ws=self.gemm_ws, stream=stream,
+                                 stages=st)
+            ev(3 + i)
         out = moe_combine_fixed_order(self.partials, self.w, out=self.out, stream=stream)
         ev(6)
         return out
+
+    def _forward(self, x, weights, logits, w_router, stream):
+        """The layer as one library call (moe_layer_forward). Shapes are taken
+        and checked as the separate calls take them."""
+        w13, w13_s, w2, w2_s = weights
+        T, H = x.shape
+        kt, S, fmt = self.kt, self.S, ACT_FORMATS[self.fmt]
+        NE, two_i, _ = w13.shape
+        I = two_i // 2
+        E = w_router.shape[0] if logits is None else logits.shape[1]
+        counts, offsets, srt, pos = self.perm
+        partials = None if self.fused else self.partials
+        f32, i32, u8, bf16 = torch.float32, torch.int32, torch.uint8, torch.bfloat16
+        need = [(x, bf16, (T, H), "x"), (w13, u8, (NE, two_i, H // 2), "w13"),
+                (w13_s, u8, (NE, two_i, H // 32), "w13_s"), (w2, u8, (NE, H, I // 2), "w2"),
+                (w2_s, u8, (NE, H, I // 32), "w2_s"), (self.ids, i32, (T, kt), "topk_ids"),
+                (self.w, f32, (T, kt), "topk_w"), (offsets, i32, (NE + 1,), "offsets"),
+                (srt, i32, (T * kt,), "sorted"), (self.out, bf16, (T, H), "out")]
+        if logits is None:
+            need += [(w_router, bf16, (E, H), "w_router"), (self.logits, f32, (T, E), "logits")]
+        else:
+            need.append((logits, f32, (T, E), "logits"))
+        if partials is not None:
+            need.append((partials, f32, (T * kt, H), "partials"))
+        for t, dtype, shape, name in need:
+            if t.dtype is not dtype or t.shape != shape or not t.is_contiguous() or not t.is_cuda:
+                _need(t, dtype, shape, name)
+        a = _LayerArgs(
+            T, H, E, self.k, S, I, NE, fmt, int(self.fused), x.data_ptr(),
+            None if logits is None else logits.data_ptr(),
+            w_router.data_ptr() if logits is None else None, self.logits.data_ptr(),
+            w13.data_ptr(), w13_s.data_ptr(), w2.data_ptr(), w2_s.data_ptr(), self.ids.data_ptr(),
+            self.w.data_ptr(), counts.data_ptr(), offsets.data_ptr(), srt.data_ptr(),
+            pos.data_ptr(), self.perm_ws.data_ptr(), self.perm_ws.numel(), self.gemm_ws.data_ptr(),
+            self.gemm_ws.numel(), None if partials is None else partials.data_ptr(),
+            self.out.data_ptr())
+        s = torch.cuda.current_stream() if stream is None else stream
+        _check(lib.moe_layer_forward(ctypes.byref(a), s.cuda_stream), "moe_layer_forward")
+        return self.out
 
     def capture(self, x, weights, logits=None, w_router=None):
         """Record one ``forward`` into a HIP graph, so that a decode step is one
