@@ -183,6 +183,7 @@ static int max_lds_per_block() {
 // 38; row-block / tiled 900 / 927 at 53, 990 / 967 at 70.
 constexpr int kTiledMinRows = 64;
 constexpr int kBlockMinRows = 10;
+constexpr int kBf16TiledMinRows = 18;
 
 struct Geometry {
   bool s1_tiled, s2_tiled;
@@ -192,10 +193,13 @@ struct Geometry {
 
 static Geometry geometry(const GemmArgs& a) {
   const long A = (long)a.T * a.k_total;
-  // the BF16 contract: its LDS-tiled kernel takes any K (a multiple of 128)
   if (a.fmt == kFmtBf16) {
-    const bool many_bf = A >= (long)kTiledMinRows * a.NE;
-    return Geometry{many_bf, many_bf, false};
+    // Row-block or streaming by rows alone. Layer us, streaming / row-block:
+    // 682 / 823 at 11.7 rows per expert, 894 / 883 at 17.5, 1280 / 940 at 28,
+    // 1650 / 1070 at 38.5.
+    Geometry g{};
+    g.s1_tiled = g.s2_tiled = A >= (long)kBf16TiledMinRows * a.NE;
+    return g;
   }
   const bool rows = A >= (long)kTiledMinRows * a.NE;
   const bool many =
@@ -224,7 +228,7 @@ bool fused_combine_ok(const GemmArgs& a) {
 // The row-tile lists of the two stages (stage 2 shares stage 1's when their
 // tiles have as many rows).
 struct Lists {
-  int TR;  // row tile of the LDS-tiled geometry
+  int TR;  // row tile of the LDS-tiled geometry (BF16 contract: of its 128-row tiles)
   int BM1, BM2;
   TileArgs t1, t2;
 };
@@ -233,12 +237,9 @@ static Lists tile_lists(const GemmArgs& a, const GemmWorkspace& w, const Geometr
   const bool bf = a.fmt == kFmtBf16;
   const long A = (long)a.T * a.k_total;
   Lists l;
-  l.TR = tiled_rows(A, a.NE);
-  l.BM1 = g.s1_block ? block_rows()
-                     : g.s1_tiled ? (bf ? bf16_rows() : l.TR) : (bf ? bf16_stream_rows() : 16);
-  l.BM2 = g.s2_block   ? block_rows()
-          : g.s2_tiled ? (bf ? bf16_rows() : l.TR)
-                       : (g.s2_short ? short_rows() : (bf ? bf16_stream_rows() : 16));
+  l.TR = bf ? bf16_rows() : tiled_rows(A, a.NE);
+  l.BM1 = g.s1_block ? block_rows() : g.s1_tiled ? l.TR : 16;
+  l.BM2 = g.s2_block ? block_rows() : g.s2_tiled ? l.TR : g.s2_short ? short_rows() : 16;
   uint8_t* lists = a.ws + w.off[4];
   l.t1 = tile_list(lists, A, a.NE, l.BM1);
   l.t2 = l.BM2 == l.BM1 ? l.t1 : tile_list(lists + (w.off[5] - w.off[4]) / 2, A, a.NE, l.BM2);
@@ -299,7 +300,8 @@ static hipError_t launch_geometry(const GemmArgs& a, const GemmWorkspace& w, int
     p1.I = a.I;
     p1.k_total = a.k_total;
     p1.t = t1;
-    if (bf) (g.s1_tiled ? launch_s1_bf16 : launch_s1_bf16_stream)(p1, t1.mt_bound, s);
+    if (bf && g.s1_tiled) launch_s1_bf16(p1, t1.mt_bound, s);
+    else if (bf) launch_s1_bf16_stream(p1, t1.mt_bound, s);
     else if (g.s1_block) launch_s1_block(p1, t1.mt_bound, a.fmt, s);
     else if (g.s1_tiled) launch_s1_tiled(p1, t1.mt_bound, a.fmt, TR, s);
     else launch_s1_stream(p1, t1.mt_bound, a.fmt, s);
@@ -316,7 +318,8 @@ static hipError_t launch_geometry(const GemmArgs& a, const GemmWorkspace& w, int
     p2.I = a.I;
     p2.t = t2;
     if (a.out) launch_s2c_stream(S2CArgs{p2, a.topk_w, a.out, a.T, a.k_total}, a.fmt, s);
-    else if (bf) (g.s2_tiled ? launch_s2_bf16 : launch_s2_bf16_stream)(p2, t2.mt_bound, s);
+    else if (bf && g.s2_tiled) launch_s2_bf16(p2, t2.mt_bound, s);
+    else if (bf) launch_s2_bf16_stream(p2, t2.mt_bound, s);
     else if (g.s2_block) launch_s2_block(p2, t2.mt_bound, a.fmt, s);
     else if (g.s2_tiled) launch_s2_tiled(p2, t2.mt_bound, a.fmt, TR, s);
     else if (g.s2_short) launch_s2_short(p2, t2.mt_bound, a.fmt, s);

@@ -11,31 +11,29 @@
 // two FP4 codes times the block's E8M0 scale to two bf16, exact), so weights
 // still stream as 4.5 bits per value.
 //
-// Two geometries, chosen by rows per expert. The LDS-tiled one (below; the
-// weight-streaming one for few rows per expert follows it): workgroup tile
-// 128 sorted rows x 256 weight rows (stage 1: 128 gate rows and the matching
-// 128 up rows, so SwiGLU stays in the workgroup), K in steps of 32 (one
-// scale block); 8 waves, each one 32-row weight block x all 128 rows = 4
-// products of 32x32x16 bf16 per 16 K elements. Measured facts behind the shape: the
-// FP4 -> bf16 conversion instruction costs about 16 clocks a wave, as much
-// per step as the products, so no two waves convert the same codes (each
-// wave's weight block is the one it moves by DMA); and a 128-row weight
-// tile re-read the bf16 activation rows twice as often as this one. A tile
-// of fewer than 128 rows (decode: a few rows per expert) skips the operand
-// reads and products of its empty 32-row blocks; full tiles run a loop
-// without those tests (the tests cost full tiles ~10%). The
-// product is transposed (weights are the row operand), so a lane's
-// accumulator holds 16 weight-row values of one activation row; stage 1's
-// up waves hand their accumulators to the gate waves through LDS.
-//
-// Data movement: activation rows (64 bytes a step) and weight rows (16 bytes
-// of FP4 a step) go global -> LDS by DMA through a ring of steps; every
-// wave issues exactly 2 DMA instructions per step (rows past the tile's end
-// repeat its first row; a stage past the last step reloads the last one), so
-// one explicit vmcnt wait per step counts exactly. The tile's weight scale
-// rows (K/32 bytes each) are staged once. Activation rows are chunk-swizzled
-// (16-byte chunk c of row r at c ^ ((r >> 2) & 3)) so the operand reads do
-// not collide in LDS banks.
+// Two geometries, chosen by rows per expert. The row-block one (below; the
+// weight-streaming one for few rows per expert follows it): a workgroup of four
+// waves owns a tile of 128 sorted rows x 256 weight rows; each wave takes 64 weight
+// rows (stage 1: 32 gate rows and the matching 32 up rows, so SwiGLU stays in
+// registers) x all rows, 32x32x16 bf16 products with the weights as the row
+// operand, so a lane's accumulator holds 16 weight-row values of one activation
+// row. What bounds it is the matrix cores beside what feeds them:
+//  - the FP4 -> bf16 conversion costs a wave about 16 clocks for two codes a
+//    lane, half of the products' time at 128 rows, so no two waves convert the
+//    same codes: a wave streams its own weight rows from memory straight to
+//    registers (block layout, 16 bytes = one scale block a lane and step) and
+//    converts them there;
+//  - the activations are shared by the four waves through LDS, double-buffered
+//    in K steps of 64. With 64 weight rows a wave reads 16 KiB of them per 1024
+//    clocks of products, half of what LDS delivers to two workgroups per CU;
+//    with 32 weight rows a wave (and the weights in LDS too) LDS took longer
+//    than the products, and steps of 32 met twice the barriers.
+// K order inside a step: lane half h takes the step's 32-element block h, product
+// i its elements [8 i, 8 i + 8), the same for weights and activations.
+// 32-row blocks past the tile's last row are neither read nor multiplied.
+// Measured (H = 4096, I = 2048, 256 + 1 experts, top-8; against LDS-tiled weights
+// and 32 weight rows a wave): 8192 tokens stage 1 3.52 -> 2.5 ms (0.98 PF/s),
+// stage 2 1.68 -> 1.36, layer 5.25 -> 4.2; 3000 tokens 2.79 -> 2.2 ms.
 #include "gemm_common.h"
 #include "gemm_launch.h"
 
@@ -44,20 +42,6 @@ namespace moe {
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-
-constexpr int kBM = 128;              // sorted rows per tile
-constexpr int kBN = 256;              // weight rows per tile
-constexpr int kWaves = 8;
-constexpr int kBK = 32;               // K elements per step
-#ifndef MOE_BF16_RING
-#define MOE_BF16_RING 4
-#endif
-constexpr int kRingN = MOE_BF16_RING;  // steps in the LDS ring
-constexpr int kAS = kBM * kBK * 2;    // activation bytes per step (8 KiB)
-constexpr int kBS = kBN * kBK / 2;    // weight bytes per step (4 KiB)
-constexpr int kSlot = kAS + kBS;
-constexpr int kRingBytes = kRingN * kSlot;
-constexpr int kDmaPerStep = 2;        // DMA instructions per wave per step
 
 struct BfArgs {
   const uint8_t* act;       // stage 1: x bf16 [T, K]; stage 2: h bf16 [A, K] in sorted-row order
@@ -68,16 +52,6 @@ struct BfArgs {
   int K, N, I, H, k_total;  // N: weight rows per expert (2I or H)
   TileArgs t;
 };
-
-// Stage 1 passes the up accumulators [128 rows][128 columns] through LDS
-// after the K loop, rows padded to kExStride floats (no bank collisions).
-constexpr int kExStride = 132;
-constexpr size_t kExBytes = (size_t)kBM * kExStride * 4;
-
-size_t bf16_lds_bytes(int K) {
-  const size_t loop = kRingBytes + (size_t)kBN * (K / 32);
-  return loop > kExBytes ? loop : kExBytes;
-}
 
 // E8M0 byte -> 2^(b - 127) as fp32 (b = 0: the subnormal 2^-127; 255: NaN).
 __device__ __forceinline__ float e8m0_f32(uint32_t b) {
@@ -101,177 +75,218 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
   return f32_to_bf16_rne(a) | (f32_to_bf16_rne(b) << 16);
 }
 
-// The K loop over steps of 32: ALL runs the four row blocks; otherwise only
-// the first nmb (their reads and products).
-template <bool ALL, typename Issue>
-__device__ __forceinline__ void bf16_kloop(const uint8_t* lds, const uint8_t* sc_lds, int brow,
-                                           const int* arow, int nk, int kb, int h, Issue& issue,
-                                           v16f* acc, int nmb) {
-  uint32_t scb = sc_lds[brow * kb];  // scale byte of the next step (read one step ahead)
-  for (int k = 0; k < nk; ++k) {
-    // this wave's DMA of step k landed (later steps may be in flight), and
-    // after the barrier every wave's has, and every wave is done with step k-1
-    tvmcnt_s<(kRingN - 2) * kDmaPerStep>();
-    asm volatile("s_barrier" ::: "memory");
-    issue(k + kRingN - 1);  // into the slot of step k - 1
-    const uint8_t* as = lds + (k % kRingN) * kSlot;
-    const uint8_t* bs = as + kAS;
-    const float sc = e8m0_f32(scb);
-    scb = sc_lds[brow * kb + (k + 1 < nk ? k + 1 : k)];
+constexpr int kBM = 128;              // sorted rows per tile (four 32-row blocks)
+constexpr int kBRow = 128;            // activation bytes per row per K step of 64
+constexpr int kBSlot = kBM * kBRow;   // bytes of one LDS activation slot (16 KiB)
+constexpr int kBLoads = kBM / 32;     // activation loads per wave per step (8 rows each)
+
+// LDS byte of 16-byte chunk c of row r in an activation slot.
+__device__ __forceinline__ int bb_chunk(int r, int c) {
+  return r * kBRow + 16 * (c ^ ((r >> 1) & 7));
+}
+
+// Scale bytes of weight rows in LDS: pieces of 16 bytes (512 elements) with the
+// even blocks' eight bytes first (lane half 0), then the odd ones' (lane half
+// 1); rows kb rounded up to 16, plus 8, bytes apart.
+__host__ __device__ inline int bb_stride(int kb) { return (kb + 15) / 16 * 16 + 8; }
+
+// One wave's 64 scale rows row(0) .. row(63) of kb bytes (a multiple of 4).
+template <typename RowFn>
+__device__ __forceinline__ void bb_scales(uint8_t* dst, RowFn row, int kb, int lane) {
+  const int st = bb_stride(kb), pc = (kb + 15) / 16;
+  for (int i = lane; i < 64 * pc; i += 64) {
+    const int r = i / pc, c = i % pc;
+    const uint32_t* q = reinterpret_cast<const uint32_t*>(row(r) + 16 * c);
+    uint32_t v[4];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const v8bf wa = fp4x8_bf16(*reinterpret_cast<const uint32_t*>(bs + brow * 16 + 8 * ks + 4 * h), sc);
-      v8bf xb[4];
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        const int r = arow[mb];
-        if (ALL || mb < nmb)
-          xb[mb] = *reinterpret_cast<const v8bf*>(as + r * 64 + 16 * ((2 * ks + h) ^ ((r >> 2) & 3)));
-      }
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-        if (ALL || mb < nmb) acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, xb[mb], acc[mb], 0, 0, 0);
-    }
+    for (int j = 0; j < 4; ++j) v[j] = 16 * c + 4 * j < kb ? q[j] : 0u;
+    uint32_t* d = reinterpret_cast<uint32_t*>(dst + r * st + 16 * c);
+    d[0] = __builtin_amdgcn_perm(v[1], v[0], 0x06040200);
+    d[1] = __builtin_amdgcn_perm(v[3], v[2], 0x06040200);
+    d[2] = __builtin_amdgcn_perm(v[1], v[0], 0x07050301);
+    d[3] = __builtin_amdgcn_perm(v[3], v[2], 0x07050301);
   }
+}
+
+// The K loop of a workgroup over nst = K / 64 steps (an even number), for a tile
+// with NMB 32-row blocks. arow(r): byte offset of tile row r's activations
+// from abase; wb[n]: the wave's 32-row weight block n (uniform) at K piece 0; sc:
+// the wave's scale rows in LDS (staged by scales()).
+// The weights of step s + 2 go out after step s, into the registers just
+// multiplied, the activations of step s + 1 at its start: with the accumulators
+// there are registers for no more, and none needed (three steps of weights in
+// flight for tiles of up to 64 rows, with or without the streaming policy, ran 3
+// to 6% slower at 500 to 1500 tokens).
+template <int NMB, typename RowFn, typename ScaleFn>
+__device__ __forceinline__ void bb_kloop(uint8_t* lds, const uint8_t* abase, RowFn arow,
+                                         const uint8_t* const* wb, int K, const uint8_t* sc, int w,
+                                         int lane, v16f (*acc)[2], ScaleFn scales) {
+  const int l32 = lane & 31, h = lane >> 5, kb = K / 32, nst = K / 64;
+  uint32_t ao[kBLoads];  // activation byte of this lane at step 0
+  int aw[kBLoads];       // its LDS byte in a slot
+#pragma unroll
+  for (int i = 0; i < kBLoads; ++i) {
+    const int r = 8 * (kBLoads * w + i) + lane / 8;
+    ao[i] = arow(r) + 16 * (lane % 8);
+    aw[i] = bb_chunk(r, lane % 8);
+  }
+  // weight bytes of this lane: row l32 of the block (two 16-row groups), half h
+  // of a step's 64 elements (half of a K piece)
+  const uint32_t wo = (uint32_t)(l32 >> 4) * 16 * (uint32_t)(K / 2) + 64 * (l32 & 15) + 16 * h;
+  v4u f[2][2], fa[kBLoads];
+  auto load_a = [&](v4u* a, int s) {
+    const uint8_t* ab = abase + (size_t)s * kBRow;
+#pragma unroll
+    for (int i = 0; i < kBLoads; ++i) a[i] = ld16<false>(ab + ao[i]);
+  };
+  auto load_w = [&](v4u* q, int s) {
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+      q[n] = ld16<false>(wb[n] + (size_t)(s >> 1) * 1024 + 32 * (s & 1) + wo);
+  };
+  auto put = [&](const v4u* a, int s) {
+#pragma unroll
+    for (int i = 0; i < kBLoads; ++i)
+      *reinterpret_cast<v4u*>(lds + (s & 1) * kBSlot + aw[i]) = a[i];
+  };
+  auto sync = [&]() {  // LDS only: the loads in flight stay in flight
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    asm volatile("s_barrier" ::: "memory");
+  };
+  const uint8_t* const scl = sc + l32 * bb_stride(kb) + 8 * h;
+  const int st32 = 32 * bb_stride(kb);
+  uint32_t sv[2];  // this lane's scales of four steps
+  auto mma = [&](const v4u* q, int s) {
+    const uint8_t* st = lds + (s & 1) * kBSlot;
+    // the operands of product step i + 1 are read while i is multiplied, and no
+    // further ahead (the accumulators leave few registers)
+    v8bf x[2][NMB];
+    auto read = [&](v8bf* o, int i) {
+#pragma unroll
+      for (int m = 0; m < NMB; ++m)
+        o[m] = *reinterpret_cast<const v8bf*>(st + bb_chunk(32 * m + l32, 4 * h + i));
+    };
+    read(x[0], 0);
+    float fs[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) fs[n] = e8m0_f32((sv[n] >> (8 * (s & 3))) & 0xffu);
+    static_for<4>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (i < 3) read(x[(i + 1) & 1], i + 1);
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        const v8bf wv = fp4x8_bf16(q[n][i], fs[n]);
+#pragma unroll
+        for (int m = 0; m < NMB; ++m)
+          acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, x[i & 1][m], acc[m][n], 0, 0, 0);
+      }
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int m = 0; m < NMB; ++m)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) acc[m][n] = v16f{};
+  load_a(fa, 0);
+  load_w(f[0], 0);
+  load_w(f[1], 1);
+  scales();
+  put(fa, 0);
+  sync();
+  auto step = [&](auto J, int s, auto last) {  // step s, s % 2 == J; last: of the last two
+    constexpr int j = decltype(J)::value;
+    constexpr bool kLast = decltype(last)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!kLast || j == 0) load_a(fa, s + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if ((s & 3) == 0) {
+#pragma unroll
+      for (int n = 0; n < 2; ++n)
+        sv[n] = *reinterpret_cast<const uint32_t*>(scl + n * st32 + 2 * (s & ~7) + (s & 4));
+    }
+    mma(f[j], s);
+    if constexpr (!kLast) load_w(f[j], s + 2);
+    if constexpr (!kLast || j == 0) {
+      put(fa, s + 1);
+      sync();
+    }
+  };
+  int s = 0;
+  for (; s + 2 < nst; s += 2)
+    static_for<2>(
+        [&](auto J) { step(J, s + decltype(J)::value, std::integral_constant<bool, false>{}); });
+  static_for<2>(
+      [&](auto J) { step(J, s + decltype(J)::value, std::integral_constant<bool, true>{}); });
 }
 
 // ST = 1: gate/up + SwiGLU + bf16 h; ST = 2: down -> fp32 partials.
 template <int ST>
-__global__ __launch_bounds__(64 * kWaves) void bf16_gemm_kernel(BfArgs p) {
+__global__ __launch_bounds__(256, 2) void bf16_block_kernel(BfArgs p) {
   int4 tile;
   int nt;
   if (!tile_of_block(p.t, &tile, &nt)) return;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  const int e = __builtin_amdgcn_readfirstlane(tile.x);
-  const int row0 = __builtin_amdgcn_readfirstlane(tile.y);
-  const int nrows = __builtin_amdgcn_readfirstlane(tile.z);
+  const int e = tile.x, row0 = tile.y, nrows = tile.z;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
-  const int kb = p.K / 32, nk = kb;
-  const uint32_t ring = __builtin_amdgcn_readfirstlane(lds_addr(lds));
-  uint8_t* sc_lds = lds + kRingBytes;  // [kBN][kb] weight scale bytes
-
-  // tile weight row r -> expert weight row (stage 2: rows past H repeat row
-  // H - 1; their columns are not stored)
-  auto wrow = [&](int r) {
-    return ST == 1 ? (r < 128 ? 128 * nt + r : p.I + 128 * nt + r - 128)
-                   : (kBN * nt + r < p.H ? kBN * nt + r : p.H - 1);
+  const int kb = p.K / 32;
+  // first weight row of the wave's block n: stage 1 gate and up rows of 32 h
+  // columns, stage 2 two blocks of output columns (past H, when H % 256 == 128,
+  // the last 32 rows again; their columns are not stored)
+  const int c0 = ST == 1 ? 128 * nt + 32 * w : 256 * nt + 64 * w;
+  auto wrow = [&](int n) {
+    return ST == 1 ? (n ? p.I + c0 : c0) : (c0 + 32 * n < p.H ? c0 + 32 * n : p.H - 32);
   };
-  const uint8_t* wbase = p.w + (size_t)e * p.N * (p.K / 2);
+  const uint8_t* wb[2];
+#pragma unroll
+  for (int n = 0; n < 2; ++n)
+    wb[n] = p.w + ((size_t)e * p.N + wrow(n)) * (p.K / 2);
   const uint8_t* sbase = p.ws + (size_t)e * p.N * kb;
-
-  // DMA sources of this lane: the activation instruction covers tile rows
-  // 16 w + lane / 4, chunk slot lane % 4 (global chunk slot ^ f(row)); the
-  // weight instruction covers tile row 32 w + lane (lanes < 32).
-  uint32_t aoff;
-  {
-    const int r = 16 * w + (lane >> 2);
-    const int rr = row0 + (r < nrows ? r : 0);
-    const int src = ST == 1 ? p.sorted[rr] / p.k_total : rr;
-    const int c = (lane & 3) ^ ((r >> 2) & 3);
-    aoff = (uint32_t)src * (uint32_t)(p.K * 2) + 16 * c;
-  }
-  // weights in the block layout: step s (16 bytes of a row) is bytes
-  // 16 (s % 4) of K piece s / 4 of the row's 16-row group
-  const int wr = wrow(32 * w + l32);
-  const uint32_t boff = (uint32_t)(wr & ~15) * (uint32_t)(p.K / 2) + 64 * (uint32_t)(wr & 15);
-  // step s's slot; past the last step the slot gets the last step again
-  auto issue = [&](int s) {
-    const uint32_t slot = ring + (uint32_t)((s % kRingN) * kSlot);
-    const int step = s < nk ? s : nk - 1;
-    sdma16(p.act, aoff + (uint32_t)step * 64, slot + 16 * w * 64);
-    if (lane < 32)
-      sdma16(wbase, boff + (uint32_t)(step >> 2) * 1024 + 16 * (uint32_t)(step & 3),
-             slot + kAS + 32 * w * 16);
+  uint8_t* sc = lds + 2 * kBSlot + 64 * w * bb_stride(kb);
+  auto scales = [&]() {
+    bb_scales(sc, [&](int r) { return sbase + (size_t)(wrow(r >> 5) + (r & 31)) * kb; }, kb, lane);
   };
-
-  // weight scale rows of the tile (stage 1: the 128 gate rows, then the 128
-  // up rows; stage 2: the rows below H)
-  {
-    const int nblk = ST == 1 ? 2 : 1, rows = kBN / nblk;
-    const int vrows = ST == 1 ? rows : (p.H - kBN * nt < rows ? p.H - kBN * nt : rows);
-    const int bytes = vrows * kb;
-    const uint32_t sl = ring + kRingBytes;
-    for (int b = 0; b < nblk; ++b) {
-      const uint8_t* src = sbase + (size_t)wrow(b * rows) * kb;
-      for (int o = 1024 * w; o < bytes; o += 1024 * kWaves)
-        if (o + 16 * lane < bytes) sdma16(src, (uint32_t)(o + 16 * lane), sl + b * rows * kb + o);
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < kRingN - 1; ++s) issue(s);
-  // every wave's share of the scale rows and of the first stages has landed
-  // before any wave reads LDS
-  tvmcnt_s<0>();
-  asm volatile("s_barrier" ::: "memory");
-
-  // operand rows of this lane: the wave's one weight block (tile rows
-  // 32 w .. 32 w + 31, the rows it moves itself, so no two waves convert the
-  // same codes) against all four activation blocks
-  const int brow = 32 * w + l32;
-  int arow[4];
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) arow[mb] = 32 * mb + l32;
-  v16f acc[4];
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) acc[mb] = v16f{};
-
-  // row blocks holding tile rows: a tile short of 128 rows skips the reads
-  // and products of the others (they stay zero and are not stored); full
-  // tiles run the loop without the per-block tests
-  const int nmb = __builtin_amdgcn_readfirstlane((nrows + 31) / 32);
-  if (nmb >= 4) bf16_kloop<true>(lds, sc_lds, brow, arow, nk, kb, h, issue, acc, 4);
-  else bf16_kloop<false>(lds, sc_lds, brow, arow, nk, kb, h, issue, acc, nmb);
-  tvmcnt_s<0>();  // the ring's last (repeated) loads
-
+  auto arow = [&](int r) {
+    const int rr = row0 + (r < nrows ? r : 0);
+    return (uint32_t)(ST == 1 ? p.sorted[rr] / p.k_total : rr) * (uint32_t)(p.K * 2);
+  };
+  v16f acc[kBM / 32][2];
+  const int nmb = (nrows + 31) / 32;
+#define MOE_BB(N) bb_kloop<N>(lds, p.act, arow, wb, p.K, sc, w, lane, acc, scales)
+  if (nmb == 4) MOE_BB(4);
+  else if (nmb == 3) MOE_BB(3);
+  else if (nmb == 2) MOE_BB(2);
+  else MOE_BB(1);
+#undef MOE_BB
   // D: lane l, element i = weight row 8 (i / 4) + 4 h + i % 4 of the block,
   // activation row l % 32 of the block.
-  if constexpr (ST == 1) {
-    // waves 0-3 hold gate columns 32 w + .., waves 4-7 the matching up
-    // columns: the up waves pass theirs through LDS (the ring is free now)
-    asm volatile("s_barrier" ::: "memory");
-    float* ex = reinterpret_cast<float*>(lds);  // [128 rows][kExStride]
-    if (w >= 4) {
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+  for (int m = 0; m < kBM / 32; ++m) {
+    const int r = 32 * m + l32;
+    if (r >= nrows) continue;
+    if constexpr (ST == 1) {
+      uint8_t* dst = p.hout + ((size_t)(row0 + r) * p.I + c0 + 4 * h) * 2;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<v4f*>(ex + arow[mb] * kExStride + 32 * (w - 4) + 8 * q + 4 * h) =
-              v4f{acc[mb][4 * q], acc[mb][4 * q + 1], acc[mb][4 * q + 2], acc[mb][4 * q + 3]};
-    }
-    asm volatile("s_barrier" ::: "memory");
-    if (w < 4) {
+      for (int q = 0; q < 4; ++q) {
+        float hv[4];
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        const int m = arow[mb];
-        if (m >= nrows) continue;
-        uint8_t* dst = p.hout + ((size_t)(row0 + m) * p.I + 128 * nt + 32 * w + 4 * h) * 2;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const v4f U = *reinterpret_cast<const v4f*>(ex + m * kExStride + 32 * w + 8 * q + 4 * h);
-          float hv[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float G = acc[mb][4 * q + j];
-            hv[j] = G * U[j] / (1.0f + expf(-G));
-          }
-          *reinterpret_cast<uint2*>(dst + 16 * q) =
-              make_uint2(bf16_pair(hv[0], hv[1]), bf16_pair(hv[2], hv[3]));
+        for (int j = 0; j < 4; ++j) {
+          const float Gv = acc[m][0][4 * q + j], U = acc[m][1][4 * q + j];
+          hv[j] = Gv * U / (1.0f + expf(-Gv));
         }
+        *reinterpret_cast<uint2*>(dst + 16 * q) =
+            make_uint2(bf16_pair(hv[0], hv[1]), bf16_pair(hv[2], hv[3]));
       }
-    }
-  } else {
-    if (kBN * nt + 32 * w < p.H) {  // columns past H (H % 256 == 128) are not stored
+    } else {
+      float* dst = p.partials + (size_t)p.sorted[row0 + r] * p.H + c0 + 4 * h;
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        const int m = arow[mb];
-        if (m >= nrows) continue;
-        const size_t a = (size_t)p.sorted[row0 + m];
-        float* dst = p.partials + a * p.H + kBN * nt + 32 * w + 4 * h;
+      for (int n = 0; n < 2; ++n) {
+        if (c0 + 32 * n >= p.H) continue;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<v4f*>(dst + 8 * q) =
-              v4f{acc[mb][4 * q], acc[mb][4 * q + 1], acc[mb][4 * q + 2], acc[mb][4 * q + 3]};
+          *reinterpret_cast<v4f*>(dst + 32 * n + 8 * q) =
+              v4f{acc[m][n][4 * q], acc[m][n][4 * q + 1], acc[m][n][4 * q + 2], acc[m][n][4 * q + 3]};
       }
     }
   }
@@ -453,8 +468,8 @@ static void launch_bf(const BfArgs& p0, long mt, int n_ntiles, hipStream_t s) {
   p.t.n_ntiles = n_ntiles;
   p.t.ngroup = n_group_of(n_ntiles);
   const long n = mt * n_ntiles;
-  hipLaunchKernelGGL((bf16_gemm_kernel<ST>), dim3((int)((n + 7) / 8 * 8)), dim3(64 * kWaves),
-                     bf16_lds_bytes(p.K), s, p);
+  const size_t lds = (size_t)2 * kBSlot + (size_t)256 * bb_stride(p.K / 32);
+  hipLaunchKernelGGL((bf16_block_kernel<ST>), dim3((int)((n + 7) / 8 * 8)), dim3(256), lds, s, p);
 }
 
 void launch_s1_bf16(const S1Args& a, long mt, hipStream_t s) {
@@ -464,14 +479,12 @@ void launch_s1_bf16(const S1Args& a, long mt, hipStream_t s) {
 
 void launch_s2_bf16(const S2Args& a, long mt, hipStream_t s) {
   BfArgs p{a.hq, a.sorted, a.w2, a.w2s, nullptr, a.partials, a.I, a.H, a.I, a.H, 1, a.t};
-  launch_bf<2>(p, mt, (a.H + kBN - 1) / kBN, s);
+  launch_bf<2>(p, mt, (a.H + 255) / 256, s);
 }
 
 // Streaming geometry: 32 h columns per wave in stage 1 (2 gate + 2 up
 // blocks), 64 output columns in stage 2; tiles of up to 16 rows.
 constexpr int kBfS1 = 2, kBfS2 = 4;
-
-int bf16_stream_rows() { return 16; }
 
 // K split over two waves when each gets at least two steps of 128 and the
 // same number of them.

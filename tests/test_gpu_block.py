@@ -56,3 +56,19 @@ def test_block_rule_keeps_the_fused_shapes_streaming(m):
     a = a.clone()
     _, b = run_layer(m, cfg, gc.to_dev_bf16(inp.x), w, logits=inp.logits, fused=True)
     assert np.array_equal(gc.bf16_bits(a), gc.bf16_bits(b))
+
+
+@pytest.mark.parametrize("T,H,I,E,k,S,routing", [
+    (36, 128, 128, 2, 1, 0, "normal"),      # the rule's lowest rows per expert; one group of K steps
+    (300, 384, 640, 5, 2, 0, "normal"),     # K steps 6 and 10, H % 256 == 128, 33 .. 128 rows
+    (500, 512, 256, 3, 1, 1, "zipf"),       # several tiles an expert, every block count
+    (260, 1024, 512, 12, 4, 1, "zipf"),     # empty experts and full tiles
+])
+def test_bf16_row_block(m, T, H, I, E, k, S, routing):
+    from tests.test_gpu_bf16 import check, run
+    cfg = synth.LayerConfig("bfblock", T, H, E, k, I, S, routing, T, zipf_empty=E // 4)
+    inp = synth.make_inputs(cfg)
+    log(f"bf16 row-block {(T, H, I, E, k, S, routing)}")
+    layer, out = run(m, cfg, inp)
+    assert m.moe_last_variant() == m.VARIANT_BF16
+    check(cfg, inp, layer, out, np.arange(cfg.T))
