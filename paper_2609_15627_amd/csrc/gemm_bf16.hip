@@ -297,11 +297,12 @@ __global__ __launch_bounds__(256, 2) void bf16_block_kernel(BfArgs p) {
 // (decode): a workgroup takes a tile of up to 16 sorted rows and NBW blocks
 // of 16 weight rows (stage 1: NBW gate blocks and the matching up blocks),
 // so every weight byte is read once, straight into registers, and expanded
-// there. With KW = 2 its two waves each stream half of the K steps and wave
-// 0 adds wave 1's fp32 sums (first half + second half, through LDS) before
-// the epilogue: the last, partly filled round of a streaming launch is
-// bound by each wave's own loads in flight, and half the K extent per wave
-// halves it. 16x16x32 bf16 products with the weights as the row
+// there. With KW = 4 (or 2) its waves each stream a quarter (half) of the K steps
+// and wave 0 adds the others' fp32 sums ((s0 + s1) + (s2 + s3), through LDS)
+// before the epilogue: the last, partly filled round of a streaming launch is
+// bound by each wave's own loads in flight, and a smaller K share per wave
+// shortens it (decode layer, two waves against four: 520 -> 492 us; 16 tokens
+// 260 -> 243, 128 tokens 611 -> 571). 16x16x32 bf16 products with the weights as the row
 // operand: lane l supplies weight row l % 16 and activation row l % 16, and
 // its accumulator holds weight rows 4 (l / 16) .. +3 of activation row l % 16.
 // K order: in each K step of 128, lane group g = l / 16 takes the physical
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(64 * KW) void bf16_stream_kernel(BfArgs p) {
   if (!tile_of_block(p.t, &tile, &nt)) return;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int e = tile.x, row0 = tile.y, nrows = tile.z;
-  const int kw = KW == 2 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+  const int kw = KW > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
   const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
   const int kb = p.K / 32, nst = p.K / 128;
   const int s_lo = kw * (nst / KW), s_hi = s_lo + nst / KW;  // this wave's K steps
@@ -380,7 +381,7 @@ __global__ __launch_bounds__(64 * KW) void bf16_stream_kernel(BfArgs p) {
   load(f0);
   // weight scale rows of the tile: [NB * 16 rows][kb bytes] (stage 1: the gate
   // rows, then the up rows)
-  // (with KW = 2: wave 0 the first half of them, wave 1 the second)
+  // (shared out to the waves when there are several)
   const uint8_t* sbase = p.ws + (size_t)e * p.N * kb;
   if constexpr (ST == 1) {
     if (KW == 1 || kw == 0) dma_rows16(lds, sbase + (size_t)wrow(0) * kb, NBW * 16 * kb, lane);
@@ -389,11 +390,11 @@ __global__ __launch_bounds__(64 * KW) void bf16_stream_kernel(BfArgs p) {
   } else if constexpr (KW == 1) {
     dma_rows16(lds, sbase + (size_t)wrow(0) * kb, NB * 16 * kb, lane);
   } else {
-    const int hb = NB * 8 * kb;  // bytes of half the rows
+    const int hb = NB * 16 / KW * kb;  // bytes of this wave's share of the rows
     dma_rows16(lds + kw * hb, sbase + (size_t)wrow(0) * kb + kw * hb, hb, lane);
   }
   wait_all_vmem();
-  if constexpr (KW == 2) __syncthreads();  // the other wave's scale rows landed
+  if constexpr (KW > 1) __syncthreads();  // the other waves' scale rows landed
 
   v4f acc[NB];
 #pragma unroll
@@ -426,16 +427,20 @@ __global__ __launch_bounds__(64 * KW) void bf16_stream_kernel(BfArgs p) {
   } else {
     mma(f0, s);
   }
-  if constexpr (KW == 2) {  // first half + second half, in wave 0
+  if constexpr (KW > 1) {  // s0 + s1, or (s0 + s1) + (s2 + s3), in wave 0
     v4f* red = reinterpret_cast<v4f*>(lds + NB * 16 * kb);
-    if (kw == 1) {
+    if (kw > 0) {
 #pragma unroll
-      for (int n = 0; n < NB; ++n) red[n * 64 + lane] = acc[n];
+      for (int n = 0; n < NB; ++n) red[((kw - 1) * NB + n) * 64 + lane] = acc[n];
     }
     __syncthreads();
-    if (kw == 1) return;
+    if (kw > 0) return;
 #pragma unroll
-    for (int n = 0; n < NB; ++n) acc[n] = acc[n] + red[n * 64 + lane];
+    for (int n = 0; n < NB; ++n) {
+      acc[n] = acc[n] + red[n * 64 + lane];
+      if constexpr (KW == 4)
+        acc[n] = acc[n] + (red[(NB + n) * 64 + lane] + red[(2 * NB + n) * 64 + lane]);
+    }
   }
 
   if (c16 >= nrows) return;
@@ -486,38 +491,36 @@ void launch_s2_bf16(const S2Args& a, long mt, hipStream_t s) {
 // blocks), 64 output columns in stage 2; tiles of up to 16 rows.
 constexpr int kBfS1 = 2, kBfS2 = 4;
 
-// K split over two waves when each gets at least two steps of 128 and the
-// same number of them.
-static bool bf_split(int K) { return K % 256 == 0 && K >= 512; }
+// Waves that split K: four, or else two, when each gets at least two steps of 128
+// and the same number of them.
+static int bf_split(int K) {
+  if (K % 512 == 0 && K >= 1024) return 4;
+  return K % 256 == 0 && K >= 512 ? 2 : 1;
+}
+
+template <int ST, int NBW>
+static void launch_bf_stream(const BfArgs& p0, long mt, int ntl, hipStream_t s) {
+  BfArgs p = p0;
+  p.t.n_ntiles = ntl;
+  p.t.ngroup = n_group_of(ntl);
+  constexpr int NB = ST == 1 ? 2 * NBW : NBW;
+  const long n = mt * ntl;
+  const int kw = bf_split(p.K);
+  const dim3 grid((int)((n + 7) / 8 * 8));
+  const size_t lds = (size_t)NB * 16 * (p.K / 32) + (size_t)(kw - 1) * NB * 64 * 16;
+  const auto k = kw == 4 ? bf16_stream_kernel<ST, NBW, 4>
+                 : kw == 2 ? bf16_stream_kernel<ST, NBW, 2> : bf16_stream_kernel<ST, NBW, 1>;
+  hipLaunchKernelGGL(k, grid, dim3(64 * kw), lds, s, p);
+}
 
 void launch_s1_bf16_stream(const S1Args& a, long mt, hipStream_t s) {
   BfArgs p{a.xq, a.sorted, a.w13, a.w13s, a.hq, nullptr, a.H, 2 * a.I, a.I, a.H, a.k_total, a.t};
-  const int ntl = a.I / (kBfS1 * 16);
-  p.t.n_ntiles = ntl;
-  p.t.ngroup = n_group_of(ntl);
-  const long n = mt * ntl;
-  const dim3 grid((int)((n + 7) / 8 * 8));
-  const size_t lds = (size_t)2 * kBfS1 * 16 * (a.H / 32);
-  if (bf_split(a.H))
-    hipLaunchKernelGGL((bf16_stream_kernel<1, kBfS1, 2>), grid, dim3(128),
-                       lds + (size_t)2 * kBfS1 * 64 * 16, s, p);
-  else
-    hipLaunchKernelGGL((bf16_stream_kernel<1, kBfS1, 1>), grid, dim3(64), lds, s, p);
+  launch_bf_stream<1, kBfS1>(p, mt, a.I / (kBfS1 * 16), s);
 }
 
 void launch_s2_bf16_stream(const S2Args& a, long mt, hipStream_t s) {
   BfArgs p{a.hq, a.sorted, a.w2, a.w2s, nullptr, a.partials, a.I, a.H, a.I, a.H, 1, a.t};
-  const int ntl = a.H / (kBfS2 * 16);
-  p.t.n_ntiles = ntl;
-  p.t.ngroup = n_group_of(ntl);
-  const long n = mt * ntl;
-  const dim3 grid((int)((n + 7) / 8 * 8));
-  const size_t lds = (size_t)kBfS2 * 16 * (a.I / 32);
-  if (bf_split(a.I))
-    hipLaunchKernelGGL((bf16_stream_kernel<2, kBfS2, 2>), grid, dim3(128),
-                       lds + (size_t)kBfS2 * 64 * 16, s, p);
-  else
-    hipLaunchKernelGGL((bf16_stream_kernel<2, kBfS2, 1>), grid, dim3(64), lds, s, p);
+  launch_bf_stream<2, kBfS2>(p, mt, a.H / (kBfS2 * 16), s);
 }
 
 }  // namespace moe

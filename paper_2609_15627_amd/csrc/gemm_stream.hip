@@ -1,6 +1,6 @@
 // a5 / a6: grouped FP4 expert GEMMs, weight-streaming geometry with register
-// double or triple buffering (one wave per workgroup, or for stage 1 two
-// waves that split the K extent).
+// double buffering (four waves per workgroup that split the K extent in stage 1,
+// two in stage 2, one for the K extents that do not divide).
 //
 // Work item: (row tile of up to 16 sorted rows of one expert, N tile). Every
 // workgroup streams its N tile of the expert's packed FP4 weights from HBM
@@ -214,143 +214,128 @@ __device__ __forceinline__ void stream_k(const uint8_t* a_row, const uint8_t* co
   }
 }
 
-// The same K loop with three register buffers, for a compile-time step
-// count NST: the codes of step c + 2 go out before the products of step c,
-// so two steps of loads are in flight while one is multiplied (the
-// products and their order are those of stream_k). A third buffer still
-// fits the two waves per SIMD the double-buffered loop runs at.
-template <int FA, int J, int NB, int NST, typename Pro>
-__device__ __forceinline__ void stream_k3(const uint8_t* a_row, const uint8_t* const* b_rows,
-                                          uint32_t xa, uint32_t wb, const uint32_t* wo, int g,
-                                          v4f* acc, Pro pro, bool av) {
-  constexpr int kc = 4 * J;
-  Frag<FA, J, NB> f[3];
+// K steps [s_lo, s_hi) of 128 elements by one of the waves that split a tile's K
+// extent. Few registers, many waves: two register buffers of one step, weights
+// and activations addressed as uniform bases (advanced by the step) plus one
+// 32-bit lane offset each, so that four waves fit a SIMD; every wave has one step
+// in flight while it multiplies the other. (Steps of 256 with three buffers and
+// 64-bit lane addresses took 228 registers, two waves a SIMD: fewer loads in
+// flight per CU and longer queues behind each.)
+// arow: byte offset of this lane's activation row from abase (rows past the
+// tile's end: the tile's first row, whose loads coalesce; their sums are never
+// stored); wb[n]: weight block n (uniform) at K piece 0. xa, wo[n]: LDS bytes of
+// this lane's activation and weight scale rows. The first step's loads go out
+// before stage() (the scale rows by DMA, and a barrier once they landed).
+template <int FA, int NB, typename Stage>
+__device__ __forceinline__ void stream_lean(const uint8_t* abase, uint32_t arow,
+                                            const uint8_t* const* wb, int s_lo, int s_hi,
+                                            uint32_t xa, const uint32_t* wo, int lane, v4f* acc,
+                                            Stage stage) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  constexpr int kStep = 4 * ActBytes<FA>::kBlock;  // activation bytes of a row per step
+  const int g = lane >> 4, c16 = lane & 15;
+  const uint32_t ao = arow + (FA == 2 ? 32 : 16) * g, wl = 64 * c16 + 16 * g;
+  using F = Frag<FA, 1, NB>;
+  F f0, f1;
+  auto load = [&](F& f, int s) {
+    __builtin_amdgcn_sched_barrier(0);
+    const uint8_t* ab = abase + (size_t)s * kStep;
+    f.a[0] = ld16<false>(ab + ao);
+    if constexpr (FA != 4) f.a[1] = ld16<false>(ab + ao + (FA == 0 ? 64 : 16));
 #pragma unroll
-  for (int q = 0; q < 3; ++q)
+    for (int n = 0; n < NB; ++n) f.b[n][0] = ld16<true>(wb[n] + (size_t)s * 1024 + wl);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mma = [&](F& f, int s) {
+    f.as = lds[xa + 4 * s + g];
 #pragma unroll
-    for (int i = 0; i < Frag<FA, J, NB>::kAV; ++i) f[q].a[i] = v4u{0u, 0u, 0u, 0u};
-  frag_codes<FA, J, NB>(f[0], a_row, b_rows, 0, 0, g, av);
-  pro();
-  wait_all_vmem();
-  frag_codes<FA, J, NB>(f[1], a_row, b_rows, 0, kc, g, av);
-  static_for<NST>([&](auto C) {
-    constexpr int c = decltype(C)::value;
-    if constexpr (c + 2 < NST)
-      frag_codes<FA, J, NB>(f[(c + 2) % 3], a_row, b_rows, 0, (c + 2) * kc, g, av);
-    frag_scales<FA, J, NB>(f[c % 3], xa, wb, wo, c * kc, g);
-    frag_mma<FA, J, NB>(f[c % 3], acc);
-  });
-}
-
-// K loop of a streaming wave: triple-buffered for steps of 8 blocks and K of
-// 1024, 2048, 4096 or 8192 (nst = 4 .. 32), double-buffered otherwise.
-template <int FA, int J, int NB, bool EVEN, typename Pro>
-__device__ __forceinline__ void stream_any(const uint8_t* a_row, const uint8_t* const* b_rows,
-                                           int nst, uint32_t xa, uint32_t wb, const uint32_t* wo,
-                                           int g, v4f* acc, Pro pro, bool av) {
-  if constexpr (EVEN && J == 2) {
-    switch (nst) {
-      case 4: return stream_k3<FA, J, NB, 4>(a_row, b_rows, xa, wb, wo, g, acc, pro, av);
-      case 8: return stream_k3<FA, J, NB, 8>(a_row, b_rows, xa, wb, wo, g, acc, pro, av);
-      case 16: return stream_k3<FA, J, NB, 16>(a_row, b_rows, xa, wb, wo, g, acc, pro, av);
-      case 32: return stream_k3<FA, J, NB, 32>(a_row, b_rows, xa, wb, wo, g, acc, pro, av);
-      default: break;
-    }
+    for (int n = 0; n < NB; ++n) f.bs[n] = lds[wo[n] + 4 * s + g];
+    frag_mma<FA, 1, NB>(f, acc);
+  };
+  int s = s_lo;
+  load(f0, s);
+  stage();
+  for (; s + 2 < s_hi; s += 2) {  // f0 holds step s
+    load(f1, s + 1);
+    mma(f0, s);
+    load(f0, s + 2);
+    mma(f1, s + 1);
   }
-  stream_k<FA, J, NB, EVEN>(a_row, b_rows, nst, xa, wb, wo, g, acc, pro, av);
+  if (s + 1 < s_hi) {
+    load(f1, s + 1);
+    mma(f0, s);
+    mma(f1, s + 1);
+  } else {
+    mma(f0, s);
+  }
 }
 
-// Steps s0 .. s0 + NST - 1 of the K loop (one wave's half of a two-wave
-// split), triple-buffered like stream_k3; sync() runs once this wave's
-// prologue DMA has landed, before any scale is read from LDS.
-template <int FA, int J, int NB, int NST, typename Pro, typename Sync>
-__device__ __forceinline__ void stream_k3h(const uint8_t* a_row, const uint8_t* const* b_rows,
-                                           uint32_t xa, uint32_t wb, const uint32_t* wo, int g,
-                                           v4f* acc, Pro pro, Sync sync, bool av, int s0) {
-  constexpr int kc = 4 * J;
-  Frag<FA, J, NB> f[3];
-#pragma unroll
-  for (int q = 0; q < 3; ++q)
-#pragma unroll
-    for (int i = 0; i < Frag<FA, J, NB>::kAV; ++i) f[q].a[i] = v4u{0u, 0u, 0u, 0u};
-  frag_codes<FA, J, NB>(f[0], a_row, b_rows, 0, s0 * kc, g, av);
-  pro();
-  wait_all_vmem();
-  sync();
-  if constexpr (NST > 1) frag_codes<FA, J, NB>(f[1], a_row, b_rows, 0, (s0 + 1) * kc, g, av);
-  static_for<NST>([&](auto C) {
-    constexpr int c = decltype(C)::value;
-    if constexpr (c + 2 < NST)
-      frag_codes<FA, J, NB>(f[(c + 2) % 3], a_row, b_rows, 0, (s0 + c + 2) * kc, g, av);
-    frag_scales<FA, J, NB>(f[c % 3], xa, wb, wo, (s0 + c) * kc, g);
-    frag_mma<FA, J, NB>(f[c % 3], acc);
-  });
-}
-
-// Stage 1 with the K extent split over the two waves of a workgroup (steps
-// of 8 blocks, NSTH per wave). A streaming launch ends with a last, partly
-// filled round of workgroups, whose rate is bound by each wave's own loads
-// in flight rather than by HBM; halving a wave's share of K halves that
-// tail (measured on the decode layer: stage 1 ~3% faster). Wave 0 stages
-// the activation and gate scale rows, wave 1 the up scale rows; wave 1
-// hands its fp32 sums over through LDS and wave 0 forms first half + second
-// half (a fixed order, so results repeat bit for bit) before the SwiGLU
-// epilogue.
-template <int FA, int NBW, int NSTH>
-__global__ __launch_bounds__(128) void s1_stream2_kernel(S1Args p) {
-  constexpr int NB = 2 * NBW, J = 2;
+// Stage 1 with the K extent split over the four waves of a workgroup (K a
+// multiple of 512). A streaming launch ends with a last, partly filled round of
+// workgroups, whose rate is bound by each wave's own loads in flight rather than
+// by HBM; a wave's smaller share of K shortens that tail. Wave 0 stages the
+// activation scale rows, waves 1 and 2 the up and gate scale rows; the sums meet
+// as (s0 + s1) + (s2 + s3) in wave 0 (a fixed order, so results repeat bit for bit)
+// before the SwiGLU epilogue.
+template <int FA, int NBW>
+__global__ __launch_bounds__(256, 4) void s1_stream2_kernel(S1Args p) {
+  constexpr int NB = 2 * NBW, KW = 4;
   constexpr int kAB = ActBytes<FA>::kBlock;
   int4 tile;
   int nt;
   if (!tile_of_block(p.t, &tile, &nt)) return;
   const int e = tile.x, row0 = tile.y, nrows = tile.z;
-  const int kw = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // K half of the wave
+  const int kw = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // K share of the wave
   const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
-  const int kb = p.H / 32;
+  const int kb = p.H / 32, nst = kb / 4;
   const int hc0 = nt * (NBW * 16);  // first h column of the workgroup
   const size_t ebase = (size_t)e * 2 * p.I;
 
-  // LDS: the scale rows as in s1_stream_kernel, then wave 1's sums [NB][64] v4f
+  // LDS: the scale rows as in s1_stream_kernel, then the other waves' sums [3][NB][64] v4f
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int half = NBW * 16 * kb;
   const int tok = p.sorted[row0 + (c16 < nrows ? c16 : 0)] / p.k_total;
-  const uint8_t* a_row = p.xq + (size_t)tok * (p.H / 32) * kAB;
-  const uint8_t* b_rows[NB];
+  const uint8_t* wb[NB];
   uint32_t wo[NB];
 #pragma unroll
   for (int b = 0; b < NBW; ++b) {
     const size_t gr = ebase + hc0 + 16 * b;  // first gate row of the group
-    b_rows[b] = p.w13 + gr * (p.H / 2) + 64 * c16;
-    b_rows[NBW + b] = p.w13 + (gr + p.I) * (p.H / 2) + 64 * c16;
-    wo[b] = (16 * b + c16) * kb;
-    wo[NBW + b] = (NBW * 16 + 16 * b + c16) * kb;
+    wb[b] = p.w13 + gr * (p.H / 2);
+    wb[NBW + b] = p.w13 + (gr + p.I) * (p.H / 2);
+    wo[b] = 16 * kb + (16 * b + c16) * kb;
+    wo[NBW + b] = 16 * kb + (NBW * 16 + 16 * b + c16) * kb;
   }
   v4f acc[NB];
 #pragma unroll
   for (int n = 0; n < NB; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-  stream_k3h<FA, J, NB, NSTH>(a_row, b_rows, c16 * kb, 16 * kb, wo, g, acc, [&]() {
-    if (kw == 0) {
-      dma_gather16(
-          lds,
-          [&](int r) {
-            const int t = p.sorted[row0 + (r < nrows ? r : 0)] / p.k_total;
-            return p.xs + (size_t)t * kb;
-          },
-          kb, lane);
-      dma_rows16(lds + 16 * kb, p.w13s + (ebase + hc0) * kb, half, lane);
-    } else {
-      dma_rows16(lds + 16 * kb + half, p.w13s + (ebase + p.I + hc0) * kb, half, lane);
-    }
-  }, [&]() { __syncthreads(); }, c16 < nrows, kw * NSTH);
+  stream_lean<FA, NB>(
+      p.xq, (uint32_t)tok * (uint32_t)(kb * kAB), wb, kw * (nst / KW), (kw + 1) * (nst / KW),
+      c16 * kb, wo, lane, acc, [&]() {
+        if (kw == 0)
+          dma_gather16(
+              lds,
+              [&](int r) {
+                const int t = p.sorted[row0 + (r < nrows ? r : 0)] / p.k_total;
+                return p.xs + (size_t)t * kb;
+              },
+              kb, lane);
+        else if (kw == 1)
+          dma_rows16(lds + 16 * kb + half, p.w13s + (ebase + p.I + hc0) * kb, half, lane);
+        else if (kw == 2)
+          dma_rows16(lds + 16 * kb, p.w13s + (ebase + hc0) * kb, half, lane);
+        wait_all_vmem();
+        __syncthreads();
+      });
   v4f* red = reinterpret_cast<v4f*>(lds + (1 + 2 * NBW) * 16 * kb);
-  if (kw == 1) {
+  if (kw > 0) {
 #pragma unroll
-    for (int n = 0; n < NB; ++n) red[n * 64 + lane] = acc[n];
+    for (int n = 0; n < NB; ++n) red[((kw - 1) * NB + n) * 64 + lane] = acc[n];
   }
   __syncthreads();
-  if (kw == 1) return;
+  if (kw > 0) return;
 #pragma unroll
-  for (int n = 0; n < NB; ++n) acc[n] = acc[n] + red[n * 64 + lane];
+  for (int n = 0; n < NB; ++n)
+    acc[n] = (acc[n] + red[n * 64 + lane]) + (red[(NB + n) * 64 + lane] + red[(2 * NB + n) * 64 + lane]);
   s1_epilogue<FA, NBW>(acc, p, row0, nrows, hc0, g, c16);
 }
 
@@ -388,7 +373,7 @@ __global__ __launch_bounds__(64) void s1_stream_kernel(S1Args p) {
   v4f acc[NB];
 #pragma unroll
   for (int n = 0; n < NB; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-  stream_any<FA, J, NB, EVEN>(a_row, b_rows, kb / (4 * J), c16 * kb, 16 * kb, wo, g, acc, [&]() {
+  stream_k<FA, J, NB, EVEN>(a_row, b_rows, kb / (4 * J), c16 * kb, 16 * kb, wo, g, acc, [&]() {
     dma_gather16(
         lds,
         [&](int r) {
@@ -428,7 +413,7 @@ __global__ __launch_bounds__(64) void s2_stream_kernel(S2Args p) {
   v4f acc[NB];
 #pragma unroll
   for (int n = 0; n < NB; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-  stream_any<FA, J, NB, EVEN>(a_row, b_rows, kb / (4 * J), c16 * kb, 16 * kb, wo, g, acc, [&]() {
+  stream_k<FA, J, NB, EVEN>(a_row, b_rows, kb / (4 * J), c16 * kb, 16 * kb, wo, g, acc, [&]() {
     dma_gather16(
         lds, [&](int r) { return p.hs + ((size_t)row0 + (r < nrows ? r : 0)) * kb; }, kb, lane);
     dma_rows16(lds + 16 * kb, p.w2s + rbase * kb, NB * 16 * kb, lane);
@@ -436,12 +421,12 @@ __global__ __launch_bounds__(64) void s2_stream_kernel(S2Args p) {
   s2_epilogue<NBW>(acc, p, row0, nrows, nc0, g, c16);
 }
 
-// Stage 2 with the K extent split over two waves, as s1_stream2_kernel
-// (wave 0 stages the activation scale rows, wave 1 the weight scale rows;
-// partial = first half + second half).
-template <int FA, int NBW, int NSTH>
-__global__ __launch_bounds__(128) void s2_stream2_kernel(S2Args p) {
-  constexpr int NB = NBW, J = 2;
+// Stage 2 with the K extent split over two waves (wave 0 stages the activation
+// scale rows, wave 1 the weight scale rows; partial = first half + second half,
+// the order that the fused down + combine repeats).
+template <int FA, int NBW>
+__global__ __launch_bounds__(128, 4) void s2_stream2_kernel(S2Args p) {
+  constexpr int NB = NBW;
   constexpr int kAB = ActBytes<FA>::kBlock;
   int4 tile;
   int nt;
@@ -449,31 +434,35 @@ __global__ __launch_bounds__(128) void s2_stream2_kernel(S2Args p) {
   const int e = tile.x, row0 = tile.y, nrows = tile.z;
   const int kw = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // K half of the wave
   const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
-  const int kb = p.I / 32;
+  const int kb = p.I / 32, nst = kb / 4;
   const int nc0 = nt * (NBW * 16);  // first output column of the workgroup
   const size_t rbase = (size_t)e * p.H + nc0;
 
   // LDS: the scale rows as in s2_stream_kernel, then wave 1's sums [NB][64] v4f
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  const size_t ar = (size_t)row0 + (c16 < nrows ? c16 : 0);
-  const uint8_t* a_row = p.hq + ar * (p.I / 32) * kAB;
-  const uint8_t* b_rows[NB];
+  const uint32_t ar = (uint32_t)(row0 + (c16 < nrows ? c16 : 0));
+  const uint8_t* wb[NB];
   uint32_t wo[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    b_rows[b] = p.w2 + (rbase + 16 * b) * (p.I / 2) + 64 * c16;
-    wo[b] = (16 * b + c16) * kb;
+    wb[b] = p.w2 + (rbase + 16 * b) * (p.I / 2);
+    wo[b] = 16 * kb + (16 * b + c16) * kb;
   }
   v4f acc[NB];
 #pragma unroll
   for (int n = 0; n < NB; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-  stream_k3h<FA, J, NB, NSTH>(a_row, b_rows, c16 * kb, 16 * kb, wo, g, acc, [&]() {
-    if (kw == 0)
-      dma_gather16(
-          lds, [&](int r) { return p.hs + ((size_t)row0 + (r < nrows ? r : 0)) * kb; }, kb, lane);
-    else
-      dma_rows16(lds + 16 * kb, p.w2s + rbase * kb, NB * 16 * kb, lane);
-  }, [&]() { __syncthreads(); }, c16 < nrows, kw * NSTH);
+  stream_lean<FA, NB>(
+      p.hq, ar * (uint32_t)(kb * kAB), wb, kw * (nst / 2), (kw + 1) * (nst / 2), c16 * kb, wo, lane,
+      acc, [&]() {
+        if (kw == 0)
+          dma_gather16(
+              lds, [&](int r) { return p.hs + ((size_t)row0 + (r < nrows ? r : 0)) * kb; }, kb,
+              lane);
+        else
+          dma_rows16(lds + 16 * kb, p.w2s + rbase * kb, NB * 16 * kb, lane);
+        wait_all_vmem();
+        __syncthreads();
+      });
   v4f* red = reinterpret_cast<v4f*>(lds + (1 + NBW) * 16 * kb);
   if (kw == 1) {
 #pragma unroll
@@ -761,18 +750,15 @@ static void launch_stream(int kb, K2 k2, K1 k1, K0 k0, long mt, int ntl, const P
 template <int FA, int NBW1>
 static void launch_s1(const S1Args& p, long mt, hipStream_t s) {
   const int kb = p.H / 32;
-  if (split_k(kb)) {  // K = 1024 .. 8192: the two-wave split
+  if (kb % 16 == 0 && kb >= 32) {
     S1Args q = p;
     const int ntl = p.I / (NBW1 * 16);
     q.t.n_ntiles = ntl;
     q.t.ngroup = n_group_of(ntl);
     const long n = mt * ntl;
-    const dim3 grid((int)((n + 7) / 8 * 8)), block(128);
-    const size_t lds = (size_t)(1 + 2 * NBW1) * 16 * kb + (size_t)2 * NBW1 * 64 * 16;
-    if (kb == 32) hipLaunchKernelGGL((s1_stream2_kernel<FA, NBW1, 2>), grid, block, lds, s, q);
-    else if (kb == 64) hipLaunchKernelGGL((s1_stream2_kernel<FA, NBW1, 4>), grid, block, lds, s, q);
-    else if (kb == 128) hipLaunchKernelGGL((s1_stream2_kernel<FA, NBW1, 8>), grid, block, lds, s, q);
-    else hipLaunchKernelGGL((s1_stream2_kernel<FA, NBW1, 16>), grid, block, lds, s, q);
+    const size_t lds = (size_t)(1 + 2 * NBW1) * 16 * kb + (size_t)3 * 2 * NBW1 * 64 * 16;
+    hipLaunchKernelGGL((s1_stream2_kernel<FA, NBW1>), dim3((int)((n + 7) / 8 * 8)), dim3(256), lds,
+                       s, q);
     return;
   }
   launch_stream(kb, s1_stream_kernel<FA, 2, NBW1, true>, s1_stream_kernel<FA, 1, NBW1, true>,
@@ -791,10 +777,7 @@ static void launch_s2(const S2Args& p, long mt, hipStream_t s) {
     const long n = mt * ntl;
     const dim3 grid((int)((n + 7) / 8 * 8)), block(128);
     const size_t lds = (size_t)(1 + NBW2) * 16 * kb + (size_t)NBW2 * 64 * 16;
-    if (kb == 32) hipLaunchKernelGGL((s2_stream2_kernel<FA, NBW2, 2>), grid, block, lds, s, q);
-    else if (kb == 64) hipLaunchKernelGGL((s2_stream2_kernel<FA, NBW2, 4>), grid, block, lds, s, q);
-    else if (kb == 128) hipLaunchKernelGGL((s2_stream2_kernel<FA, NBW2, 8>), grid, block, lds, s, q);
-    else hipLaunchKernelGGL((s2_stream2_kernel<FA, NBW2, 16>), grid, block, lds, s, q);
+    hipLaunchKernelGGL((s2_stream2_kernel<FA, NBW2>), grid, block, lds, s, q);
     return;
   }
   launch_stream(kb, s2_stream_kernel<FA, 2, NBW2, true>, s2_stream_kernel<FA, 1, NBW2, true>,
@@ -802,9 +785,10 @@ static void launch_s2(const S2Args& p, long mt, hipStream_t s) {
                 (size_t)(1 + NBW2) * 16 * kb);
 }
 
-// Steps of 256 K elements (128 when K/32 is not a multiple of 16); stage 1:
-// 32 h columns per workgroup, two waves splitting K for K = 1024 .. 8192,
-// else one wave; stage 2: one wave per workgroup, 64 output columns.
+// Stage 1: 32 h columns per workgroup, four waves splitting K where it is a
+// multiple of 512 from 1024 on, else one wave; stage 2: 64 output columns, two
+// waves for K = 1024, 2048, 4096 and 8192, else one. One wave steps 256 K
+// elements at a time (128 when K/32 is not a multiple of 16).
 void launch_s1_stream(const S1Args& p, long mt, int fa, hipStream_t s) {
   if (fa == 0) launch_s1<0, 2>(p, mt, s);
   else if (fa == 2) launch_s1<2, 2>(p, mt, s);

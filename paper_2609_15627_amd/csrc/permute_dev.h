@@ -39,10 +39,13 @@ __device__ __forceinline__ void wave_rank16(const int32_t* ids, int a, int A, in
 __device__ __forceinline__ int prefix_waves16(int32_t* cnt, int NE) {
   int c = 0;
   if ((int)threadIdx.x < NE) {
+    int n[16];  // all reads first: one LDS round trip instead of sixteen
+#pragma unroll
+    for (int v = 0; v < 16; ++v) n[v] = cnt[v * NE + threadIdx.x];
+#pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int n = cnt[v * NE + threadIdx.x];
       cnt[v * NE + threadIdx.x] = c;
-      c += n;
+      c += n[v];
     }
   }
   return c;
