@@ -395,7 +395,8 @@ moe_status moe_combine_fixed_order(const float* partials, const float* topk_w, i
  * moe_fp4_grouped_gemm_combine. Every check runs before anything is enqueued.
  * Small batches (T * (k + n_shared) <= 1024, n_experts_total <= 512, not the
  * LDS-tiled geometry) sort, build the tile lists and quantise x in one launch,
- * up to 16 tokens with the routing. */
+ * up to 16 tokens with the routing; up to 98304 assignments these steps take
+ * three launches with the routing. */
 typedef struct {
   int T, H, E, k, n_shared, I, n_experts_total; /* E: columns of the logits */
   moe_act_format f;

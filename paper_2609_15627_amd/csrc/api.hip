@@ -398,13 +398,15 @@ moe_status moe_layer_forward(const moe_layer_args* a, void* stream) {
   if (a->w_router)
     e = moe::launch_router_logits(a->x, a->w_router, T, a->H, a->E, a->logits_buf, s);
   int stages = 7;
-  const bool front = moe::front_ok(g);
-  if (e == hipSuccess && !(front && moe::front_routes(T)))
+  const bool large = moe::front_large_ok(g), front = large || moe::front_ok(g);
+  const bool routes = large || (front && moe::front_routes(T));
+  if (e == hipSuccess && !routes)
     e = moe::launch_route_topk(logits, T, a->E, a->k, a->n_shared, a->topk_ids, a->topk_w, s);
   if (e != hipSuccess) return launched(e);
   if (front) {
-    const moe::FrontIO io{moe::front_routes(T) ? logits : nullptr, a->E, a->k, a->n_shared,
-                          a->topk_ids, a->topk_w, a->counts, a->offsets, a->sorted, a->pos};
+    const moe::FrontIO io{routes ? logits : nullptr, a->E, a->k, a->n_shared, a->topk_ids,
+                          a->topk_w, a->counts, a->offsets, a->sorted, a->pos,
+                          static_cast<int32_t*>(a->perm_ws)};
     e = moe::launch_front_steps(g, io, s);
     stages = 6;
   } else {

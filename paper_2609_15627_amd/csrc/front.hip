@@ -16,6 +16,7 @@
 #include "permute_dev.h"
 #include "quant_dev.h"
 #include "route_dev.h"
+#include "tiles_dev.h"
 
 namespace moe {
 
@@ -87,6 +88,107 @@ hipError_t launch_front(const FrontArgs& a0, hipStream_t s) {
   else if (a.fmt == 0) launch_front_fmt<0>(a, s);
   else if (a.fmt == 2) launch_front_fmt<2>(a, s);
   else launch_front_fmt<4>(a, s);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Larger batches: three launches instead of five or six.
+//  1. routing and the quantisation of x side by side (routing is bound by its
+//     arg-max latency, the quantisation by memory);
+//  2. the chunk histograms of the sort (perm_hist);
+//  3. the scatter, whose workgroups add up the histograms of the chunks before
+//     theirs themselves (up to kFrontChunks chunks; a scan kernel of its own took
+//     4.9 us and a gap), beside one workgroup per row-tile list, which needs only
+//     the counts.
+// 4096 tokens, top-8 of 256, H = 4096: 42 us of kernels in five launches before.
+// ---------------------------------------------------------------------------
+constexpr int kFrontChunks = 96;
+
+template <int FMT, int EPL>
+__global__ __launch_bounds__(256) void route_quant_kernel(FrontArgs a, int nrb) {
+  if ((int)blockIdx.x < nrb) {
+    const int t = (int)blockIdx.x * 4 + (int)threadIdx.x / kWave;
+    if (t >= a.T) return;
+    const int kt = a.k + a.n_shared;
+    route_plain_token<EPL>(a.logits + (size_t)t * a.E, a.E, a.k, a.n_shared,
+                           a.ids + (size_t)t * kt, a.w + (size_t)t * kt, threadIdx.x % kWave);
+    return;
+  }
+  if constexpr (FMT >= 0) {
+    const long b = (long)(blockIdx.x - nrb) * 256 + threadIdx.x;
+    if (b < a.nblk) quant_block<FMT, true>(a.x, b, a.codes, a.scales);
+  }
+}
+
+__global__ __launch_bounds__(1024) void sort_tiles_kernel(FrontArgs a, int A, int nchunks) {
+  extern __shared__ int32_t sh[];
+  const int NE = a.NE, e = (int)threadIdx.x, chunk = (int)blockIdx.x;
+  int before = 0, c = 0;  // assignments of expert e in earlier chunks, and in all
+  if (e < NE) {
+    for (int i = 0; i < nchunks; i += 24) {  // 24 loads in flight a thread
+      int n[24];
+#pragma unroll
+      for (int j = 0; j < 24; ++j) n[j] = a.hist[(size_t)min(i + j, nchunks - 1) * NE + e];
+#pragma unroll
+      for (int j = 0; j < 24; ++j) {
+        if (i + j < nchunks) c += n[j];
+        if (i + j < min(chunk, nchunks)) before += n[j];
+      }
+    }
+  }
+  int total;
+  const int off = block_exclusive_scan_1024(c, &total);
+  if (chunk < nchunks) {
+    if (chunk == 0) {
+      if (e < NE) {
+        a.counts[e] = c;
+        a.offsets[e] = off;
+      }
+      if (e == 0) a.offsets[NE] = total;
+    }
+    perm_place_chunk(a.ids, chunk, A, NE, a.nbits, off + before, sh, a.sorted, a.pos);
+    return;
+  }
+  // a tile list
+  if (e < NE) sh[e] = off;
+  if (e == 0) sh[NE] = total;
+  __syncthreads();
+  const bool first = chunk == nchunks;
+  const TileArgs& t = first ? a.t1 : a.t2;
+  build_tiles(sh, NE, first ? a.BM1 : a.BM2, const_cast<int4*>(t.tiles),
+              const_cast<int*>(t.ntiles), const_cast<int4*>(t.chunks), const_cast<int*>(t.nchunks),
+              t.queue, sh + NE + 1);
+}
+
+template <int FMT>
+static void launch_route_quant(const FrontArgs& a, hipStream_t s) {
+  const int nrb = (a.T + 3) / 4;
+  const dim3 grid(nrb + (int)((a.nblk + 255) / 256)), block(256);
+  const int epl = (a.E + kWave - 1) / kWave;
+  if (epl <= 1) hipLaunchKernelGGL((route_quant_kernel<FMT, 1>), grid, block, 0, s, a, nrb);
+  else if (epl == 2) hipLaunchKernelGGL((route_quant_kernel<FMT, 2>), grid, block, 0, s, a, nrb);
+  else if (epl <= 4) hipLaunchKernelGGL((route_quant_kernel<FMT, 4>), grid, block, 0, s, a, nrb);
+  else hipLaunchKernelGGL((route_quant_kernel<FMT, 8>), grid, block, 0, s, a, nrb);
+}
+
+bool front_large_sizes_ok(int T, int NE, int k_total) {
+  const long A = (long)T * k_total;
+  return A > kChunk && A <= (long)kFrontChunks * kChunk && NE <= kSmallNE;
+}
+
+hipError_t launch_front_large(const FrontArgs& a0, hipStream_t s) {
+  FrontArgs a = a0;
+  a.nbits = 0;
+  while ((1 << a.nbits) < a.NE) ++a.nbits;
+  if (a.fmt == kFmtBf16) launch_route_quant<-1>(a, s);
+  else if (a.fmt == 0) launch_route_quant<0>(a, s);
+  else if (a.fmt == 2) launch_route_quant<2>(a, s);
+  else launch_route_quant<4>(a, s);
+  const int A = a.T * (a.k + a.n_shared), nchunks = (A + kChunk - 1) / kChunk;
+  const hipError_t e = launch_perm_hist(a.ids, A, a.NE, a.hist, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(sort_tiles_kernel, dim3(nchunks + (a.BM2 == a.BM1 ? 1 : 2)), dim3(1024),
+                     (size_t)17 * a.NE * sizeof(int32_t), s, a, A, nchunks);
   return hipGetLastError();
 }
 

@@ -4,97 +4,9 @@
 #include "gemm_launch.h"
 #include "moe_launch.h"
 #include "quant_dev.h"
+#include "tiles_dev.h"
 
 namespace moe {
-
-// ---------------------------------------------------------------------------
-// Tile list: expert e with c rows gets ceil(c / BM) row tiles. One block of
-// 1024 threads: tile counts, exclusive scan, then every thread fills tiles
-// i = tid, tid + 1024, ... by binary search over the per-expert tile starts.
-//
-// The work queue of the persistent tiled kernels starts at zero here; each
-// of their launches leaves it at zero when it ends.
-//
-// Chunk list (the tiled geometry launches C row tiles at a time, so that
-// they share their weight rows in L2). C = 2 (256-row tiles): an expert's
-// tiles pair up among themselves, so its weights are never split across two
-// chunks; the odd tile left over by an expert pairs with the next expert's
-// leftover. Chunk order: all within-expert pairs (expert order), then the
-// leftover pairs. C = 4 (128-row tiles): an expert's tiles in groups of
-// four, the last group of each expert padded with empty places (-1).
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void build_tiles(const int32_t* __restrict__ offsets, int NE, int BM,
-                                            int4* __restrict__ tiles, int* __restrict__ ntiles,
-                                            int4* __restrict__ chunks, int* __restrict__ nchunks,
-                                            int* __restrict__ queue) {
-  const int C = BM == 128 ? 4 : 2;  // row tiles per chunk
-  extern __shared__ int start[];  // [NE + 1]
-  int m[2], tot[3][2];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int e = threadIdx.x + 1024 * q;
-    m[q] = e < NE ? (offsets[e + 1] - offsets[e] + BM - 1) / BM : 0;
-  }
-  // exclusive prefix of: tiles, within-expert chunks (pairs, or groups of
-  // four with the last one padded), leftover singles (C = 2 only)
-  int p0[3], p1[3];
-  auto per_expert = [&](int k, int mv) {
-    if (k == 0) return mv;
-    if (C == 4) return k == 1 ? (mv + 3) / 4 : 0;
-    return k == 1 ? mv / 2 : mv % 2;
-  };
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const int v0 = per_expert(k, m[0]);
-    const int v1 = per_expert(k, m[1]);
-    p0[k] = block_exclusive_scan_1024(v0, &tot[k][0]);
-    p1[k] = block_exclusive_scan_1024(v1, &tot[k][1]) + tot[k][0];
-  }
-  const int total = tot[0][0] + tot[0][1];
-  const int pairs = tot[1][0] + tot[1][1];
-  const int singles = tot[2][0] + tot[2][1];
-  if (threadIdx.x < NE) start[threadIdx.x] = p0[0];
-  if (threadIdx.x + 1024 < NE) start[threadIdx.x + 1024] = p1[0];
-  if (threadIdx.x < kQueueInts) queue[threadIdx.x] = 0;
-  if (threadIdx.x == 0) {
-    start[NE] = total;
-    *ntiles = total;
-    *nchunks = pairs + (singles + 1) / 2;
-    if (singles & 1) chunks[pairs + singles / 2].y = -1;  // (C = 2; C = 4 has no singles)
-  }
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int e = threadIdx.x + 1024 * q;
-    if (e >= NE) continue;
-    const int ts = q ? p1[0] : p0[0], pr = q ? p1[1] : p0[1], sg = q ? p1[2] : p0[2];
-    if (C == 4) {
-      const int mq = m[q];
-      for (int j = 0; j < (mq + 3) / 4; ++j) {
-        const int b = 4 * j;
-        chunks[pr + j] = make_int4(ts + b, b + 1 < mq ? ts + b + 1 : -1, b + 2 < mq ? ts + b + 2 : -1,
-                                   b + 3 < mq ? ts + b + 3 : -1);
-      }
-      continue;
-    }
-    for (int j = 0; j < m[q] / 2; ++j) chunks[pr + j] = make_int4(ts + 2 * j, ts + 2 * j + 1, -1, -1);
-    if (m[q] & 1) {
-      int* c = reinterpret_cast<int*>(&chunks[pairs + sg / 2]);
-      c[sg & 1] = ts + m[q] - 1;
-      if ((sg & 1) == 0) c[2] = c[3] = -1;
-    }
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < total; i += 1024) {
-    int lo = 0, hi = NE;  // find e with start[e] <= i < start[e + 1]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (start[mid] <= i) lo = mid; else hi = mid;
-    }
-    const int j = i - start[lo];
-    const int r0 = offsets[lo] + j * BM;
-    tiles[i] = make_int4(lo, r0, min(BM, offsets[lo + 1] - r0), start[lo + 1] - start[lo]);
-  }
-}
 
 // The preparation launch: blocks [0, nqb) quantise x (1024 blocks of 32
 // elements each), then one block per tile list builds it (the two jobs are
@@ -112,10 +24,11 @@ __global__ __launch_bounds__(1024) void prep_kernel(const uint16_t* __restrict__
     }
     return;
   }
+  extern __shared__ int start[];  // [NE + 1]
   const bool first = (int)blockIdx.x == nqb;
   const TileArgs& t = first ? t1 : t2;
   build_tiles(offsets, NE, first ? BM1 : BM2, const_cast<int4*>(t.tiles), const_cast<int*>(t.ntiles),
-              const_cast<int4*>(t.chunks), const_cast<int*>(t.nchunks), t.queue);
+              const_cast<int4*>(t.chunks), const_cast<int*>(t.nchunks), t.queue, start);
 }
 
 static int tile_bound(long A, int NE, int BM) {
@@ -251,13 +164,16 @@ bool front_ok(const GemmArgs& a) {
   return front_sizes_ok(a.T, a.NE, a.k_total) && (a.fmt == kFmtBf16 || (!g.s1_tiled && !g.s2_tiled));
 }
 
+bool front_large_ok(const GemmArgs& a) { return front_large_sizes_ok(a.T, a.NE, a.k_total); }
+
 hipError_t launch_front_steps(const GemmArgs& a, const FrontIO& io, hipStream_t s) {
   const GemmWorkspace w = gemm_workspace(a.T, a.H, a.I, a.NE, a.k_total, a.fmt);
   const Lists l = tile_lists(a, w, geometry(a));
-  return launch_front(FrontArgs{a.x, a.fmt == kFmtBf16 ? 0 : (long)a.T * (a.H / 32),
+  const auto launch = front_ok(a) ? launch_front : launch_front_large;
+  return launch(FrontArgs{a.x, a.fmt == kFmtBf16 ? 0 : (long)a.T * (a.H / 32),
                                 a.ws + w.off[0], a.ws + w.off[1], io.logits, a.T, io.E, io.k,
                                 io.n_shared, io.ids, io.w, a.NE, 0, a.fmt, io.counts, io.offsets,
-                                io.sorted, io.pos, l.BM1, l.BM2, l.t1, l.t2},
+                                io.sorted, io.pos, io.hist, l.BM1, l.BM2, l.t1, l.t2},
                       s);
 }
 

@@ -132,7 +132,7 @@ __device__ __forceinline__ bool tile_of_block(const TileArgs& t, int4* tile, int
   return true;
 }
 
-// The steps before the expert GEMMs as one launch (front.hip).
+// The steps before the expert GEMMs as one launch, or few (front.hip).
 struct FrontArgs {
   const uint16_t* x;
   long nblk;                  // 32-element blocks of x to quantise (0 under the BF16 contract)
@@ -143,6 +143,7 @@ struct FrontArgs {
   float* w;
   int NE, nbits, fmt;
   int32_t *counts, *offsets, *sorted, *pos;
+  int32_t* hist;              // permutation workspace (launch_front_large)
   int BM1, BM2;               // rows per tile of the stages' lists
   TileArgs t1, t2;
 };
@@ -150,6 +151,8 @@ constexpr int kFrontTokens = 16;  // tokens up to which the launch routes too
 bool front_sizes_ok(int T, int NE, int k_total);
 bool front_routes(int T);
 hipError_t launch_front(const FrontArgs& a, hipStream_t s);
+bool front_large_sizes_ok(int T, int NE, int k_total);
+hipError_t launch_front_large(const FrontArgs& a, hipStream_t s);
 
 struct S1Args {
   const uint8_t *xq, *xs;      // activation codes [T, H*bits/8], scales [T, H/32]

@@ -65,21 +65,24 @@ struct GemmArgs {
 // Row-tile size of the LDS-tiled geometry: 0 (automatic), 128 or 256.
 void set_tiled_rows(int rows);
 hipError_t launch_grouped_gemm(const GemmArgs& a, int stages, hipStream_t s, int* variant);
-// The layer's steps before the GEMM stages in one launch: routing when logits
-// is given and there are few tokens (*routed tells), sort, x quantisation and
-// tile lists. Not for shapes it does not take (false; nothing enqueued): more than
-// 1024 assignments or 512 experts, or a stage on the LDS-tiled geometry, whose
-// work list has chunks.
+// The layer's steps before the GEMM stages in few launches, for the shapes that
+// front_ok (one launch: up to 1024 assignments; routing included when logits is
+// given, for few tokens) or front_large_ok (three launches, routing included)
+// take.
 struct FrontIO {
   const float* logits;
   int E, k, n_shared;
   int32_t* ids;
   float* w;
   int32_t *counts, *offsets, *sorted, *pos;
+  int32_t* hist;  // permutation workspace (front_large_ok)
 };
 bool front_ok(const GemmArgs& a);
+bool front_large_ok(const GemmArgs& a);
 bool front_routes(int T);
 hipError_t launch_front_steps(const GemmArgs& a, const FrontIO& io, hipStream_t s);
+// Per-chunk expert histograms of the assignments (hist [chunks, NE]).
+hipError_t launch_perm_hist(const int32_t* ids, int A, int NE, int32_t* hist, hipStream_t s);
 // Whether stage 2 can run fused with the combine for these dims (streaming
 // geometry chosen and every row's 16-column result fits one workgroup's LDS).
 bool fused_combine_ok(const GemmArgs& a);

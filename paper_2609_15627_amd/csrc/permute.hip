@@ -138,29 +138,16 @@ __global__ __launch_bounds__(1024) void perm_scatter16(const int32_t* __restrict
                                                        int32_t* __restrict__ sorted,
                                                        int32_t* __restrict__ pos) {
   extern __shared__ int32_t sh[];
-  int32_t* cnt = sh;            // [16][NE]
-  int32_t* base = sh + 16 * NE;  // [NE]: expert offset + this chunk's base
-  for (int i = threadIdx.x; i < 16 * NE; i += blockDim.x) cnt[i] = 0;
-  const int c = (int)threadIdx.x < NE ? counts[threadIdx.x] : 0;
   int total;
+  const int c = (int)threadIdx.x < NE ? counts[threadIdx.x] : 0;
   const int off = block_exclusive_scan_1024(c, &total);
+  int before = 0;
   if ((int)threadIdx.x < NE) {
-    base[threadIdx.x] = off + hist[(size_t)blockIdx.x * NE + threadIdx.x];
+    before = hist[(size_t)blockIdx.x * NE + threadIdx.x];
     if (blockIdx.x == 0) offsets[threadIdx.x] = off;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) offsets[NE] = total;
-  const int a = (int)blockIdx.x * kChunk + (int)threadIdx.x;
-  int e, rank;
-  bool ok;
-  wave_rank16(ids, a, A, NE, nbits, cnt, &e, &ok, &rank);
-  __syncthreads();
-  prefix_waves16(cnt, NE);
-  __syncthreads();
-  if (ok) {
-    const int dest = base[e] + cnt[(threadIdx.x / kWave) * NE + e] + rank;
-    sorted[dest] = a;
-    pos[a] = dest;
-  }
+  perm_place_chunk(ids, blockIdx.x, A, NE, nbits, off + before, sh, sorted, pos);
 }
 
 // All three steps in one workgroup of 1024 threads (A <= kChunk).
@@ -217,6 +204,12 @@ size_t permute_workspace_bytes(int T, int NE, int k_total) {
   const long A = (long)T * k_total;
   const long nchunks = (A + kChunk - 1) / kChunk;
   return (size_t)((nchunks * NE * sizeof(int32_t) + 255) / 256 * 256);
+}
+
+hipError_t launch_perm_hist(const int32_t* ids, int A, int NE, int32_t* hist, hipStream_t s) {
+  hipLaunchKernelGGL(perm_hist, dim3((A + kChunk - 1) / kChunk), dim3(256), NE * sizeof(int32_t), s,
+                     ids, A, NE, hist);
+  return hipGetLastError();
 }
 
 hipError_t launch_permute(const int32_t* ids, int T, int NE, int k_total, int32_t* counts,

@@ -51,6 +51,30 @@ __device__ __forceinline__ int prefix_waves16(int32_t* cnt, int NE) {
   return c;
 }
 
+// Places chunk `chunk` of the assignments by a workgroup of 1024 threads; thread
+// e < NE gives the chunk's first slot of its expert; sh: 17 NE ints of LDS.
+__device__ __forceinline__ void perm_place_chunk(const int32_t* __restrict__ ids, int chunk, int A,
+                                                 int NE, int nbits, int first, int32_t* sh,
+                                                 int32_t* __restrict__ sorted,
+                                                 int32_t* __restrict__ pos) {
+  int32_t* cnt = sh;             // [16][NE]
+  int32_t* base = sh + 16 * NE;  // [NE]
+  for (int i = threadIdx.x; i < 16 * NE; i += blockDim.x) cnt[i] = 0;
+  if ((int)threadIdx.x < NE) base[threadIdx.x] = first;
+  const int a = chunk * kChunk + (int)threadIdx.x;
+  int e, rank;
+  bool ok;
+  wave_rank16(ids, a, A, NE, nbits, cnt, &e, &ok, &rank);
+  __syncthreads();
+  prefix_waves16(cnt, NE);
+  __syncthreads();
+  if (ok) {
+    const int dest = base[e] + cnt[(threadIdx.x / kWave) * NE + e] + rank;
+    sorted[dest] = a;
+    pos[a] = dest;
+  }
+}
+
 // The whole sort of A <= kChunk assignments over NE <= kSmallNE experts by one
 // workgroup; sh: 17 NE ints of LDS. Thread e < NE gets its expert's count and
 // first slot.

@@ -50,9 +50,13 @@ def test_layer_forward_rejects(m, kw, status):
     (16, 512, 512, 64, 31, 1, "e4m3", "normal", True),      # k_total = 32, fused
     (64, 256, 256, 100, 16, 0, "e4m3", "zipf", False),      # 1024 assignments, empty experts
     (128, 256, 128, 130, 8, 0, "bf16", "zipf", False),      # 1024 assignments
-    (129, 256, 128, 130, 8, 0, "e4m3", "normal", False),    # more: separate launches
+    (129, 256, 128, 130, 8, 0, "e4m3", "normal", False),    # more: three launches, two chunks
+    (3000, 256, 128, 511, 31, 1, "e2m1", "zipf", False),    # 94 chunks, NE = 512, k_total = 32
+    (3073, 256, 128, 100, 32, 0, "e4m3", "normal", False),  # 97 chunks: separate launches
+    (2050, 256, 256, 40, 3, 1, "e2m3", "router", False),    # two lists (short-K stage 2)
     (300, 512, 512, 4, 2, 1, "bf16", "normal", False),      # LDS-tiled bf16, 128-row tiles
     (300, 512, 512, 4, 2, 1, "e4m3", "normal", False),      # LDS-tiled: separate launches
+    (1100, 512, 512, 3, 2, 1, "e4m3", "normal", False),     # LDS-tiled, three launches
     (400, 512, 256, 6, 2, 0, "e4m3", "normal", False),      # tiled stage 1, short-K stage 2
 ])
 def test_layer_forward_is_the_separate_calls(m, T, H, I, E, k, S, fmt, routing, fused):
