@@ -29,9 +29,7 @@
 //    step loop has no DMA, no stores and no wave-wide branch around a load;
 //    each step's loads go out as one group ahead of the products that do not
 //    need them;
-//  - a decode tile holds two or three of its 16 rows: lanes of the rows past
-//    the end skip their activation loads (lane-masked; they multiply zeros),
-//    which made stage 1 about 3% faster.
+//  - many light waves beat few with deep buffers (stream_lean below).
 //
 // Stage 1 (gate/up): each wave owns 16*NBW h columns; it streams those gate
 // rows and the matching up rows, so SwiGLU and the per-32 re-quantisation of
@@ -170,47 +168,25 @@ __device__ __forceinline__ void frag_mma(const Frag<FA, J, NB>& f, v4f* acc) {
   });
 }
 
-// The K loop of one wave: nst steps of 4J blocks, double-buffered in
-// registers. pro() runs right after the first step's code loads are issued
-// (it stages the scale rows, so both latencies overlap). With nst even
-// (EVEN) the loop runs step pairs with no branch around a load; odd nst
-// (K/32 not a multiple of 8) takes a plain loop.
+// The plain K loop of one wave: nst steps of 4J blocks, pro() (which stages the
+// scale rows) first. The fused kernel's, for odd step counts.
 // av: this lane's activation row is a row of the tile (lanes past the end
 // skip their activation loads and multiply zeros; rows are independent in
 // the product, and those accumulator rows are never stored).
-template <int FA, int J, int NB, bool EVEN, typename Pro>
+template <int FA, int J, int NB, typename Pro>
 __device__ __forceinline__ void stream_k(const uint8_t* a_row, const uint8_t* const* b_rows,
                                          int nst, uint32_t xa, uint32_t wb, const uint32_t* wo,
                                          int g, v4f* acc, Pro pro, bool av = true) {
   constexpr int kc = 4 * J;
-  Frag<FA, J, NB> f0, f1;
+  Frag<FA, J, NB> f;
 #pragma unroll
-  for (int i = 0; i < Frag<FA, J, NB>::kAV; ++i) f0.a[i] = f1.a[i] = v4u{0u, 0u, 0u, 0u};
-  if constexpr (EVEN) {
-    frag_codes<FA, J, NB>(f0, a_row, b_rows, 0, 0, g, av);
-    pro();
-    wait_all_vmem();  // the first step and the scale rows are needed next anyway
-    for (int c = 0; c + 2 < nst; c += 2) {  // f0 holds step c
-      frag_codes<FA, J, NB>(f1, a_row, b_rows, 0, (c + 1) * kc, g, av);
-      frag_scales<FA, J, NB>(f0, xa, wb, wo, c * kc, g);
-      frag_mma<FA, J, NB>(f0, acc);
-      frag_codes<FA, J, NB>(f0, a_row, b_rows, 0, (c + 2) * kc, g, av);
-      frag_scales<FA, J, NB>(f1, xa, wb, wo, (c + 1) * kc, g);
-      frag_mma<FA, J, NB>(f1, acc);
-    }
-    frag_codes<FA, J, NB>(f1, a_row, b_rows, 0, (nst - 1) * kc, g, av);
-    frag_scales<FA, J, NB>(f0, xa, wb, wo, (nst - 2) * kc, g);
-    frag_mma<FA, J, NB>(f0, acc);
-    frag_scales<FA, J, NB>(f1, xa, wb, wo, (nst - 1) * kc, g);
-    frag_mma<FA, J, NB>(f1, acc);
-  } else {
-    pro();
-    wait_all_vmem();
-    for (int c = 0; c < nst; ++c) {
-      frag_codes<FA, J, NB>(f0, a_row, b_rows, 0, c * kc, g, av);
-      frag_scales<FA, J, NB>(f0, xa, wb, wo, c * kc, g);
-      frag_mma<FA, J, NB>(f0, acc);
-    }
+  for (int i = 0; i < Frag<FA, J, NB>::kAV; ++i) f.a[i] = v4u{0u, 0u, 0u, 0u};
+  pro();
+  wait_all_vmem();
+  for (int c = 0; c < nst; ++c) {
+    frag_codes<FA, J, NB>(f, a_row, b_rows, 0, c * kc, g, av);
+    frag_scales<FA, J, NB>(f, xa, wb, wo, c * kc, g);
+    frag_mma<FA, J, NB>(f, acc);
   }
 }
 
@@ -270,16 +246,16 @@ __device__ __forceinline__ void stream_lean(const uint8_t* abase, uint32_t arow,
   }
 }
 
-// Stage 1 with the K extent split over the four waves of a workgroup (K a
-// multiple of 512). A streaming launch ends with a last, partly filled round of
+// Stage 1 with the K extent split over the KW waves of a workgroup. A streaming launch ends with a last, partly filled round of
 // workgroups, whose rate is bound by each wave's own loads in flight rather than
 // by HBM; a wave's smaller share of K shortens that tail. Wave 0 stages the
-// activation scale rows, waves 1 and 2 the up and gate scale rows; the sums meet
-// as (s0 + s1) + (s2 + s3) in wave 0 (a fixed order, so results repeat bit for bit)
+// activation scale rows, others (if any) the up and gate scale rows; the sums
+// meet as (s0 + s1) + (s2 + s3) in wave 0 (a fixed order, so results repeat bit for bit)
 // before the SwiGLU epilogue.
-template <int FA, int NBW>
-__global__ __launch_bounds__(256, 4) void s1_stream2_kernel(S1Args p) {
-  constexpr int NB = 2 * NBW, KW = 4;
+template <int FA, int NBW, int KW>
+__global__ __launch_bounds__(64 * KW, 4) void s1_stream2_kernel(S1Args p) {
+  static_assert(NBW % 2 == 0, "a quantisation block spans two 16-column tiles");
+  constexpr int NB = 2 * NBW;
   constexpr int kAB = ActBytes<FA>::kBlock;
   int4 tile;
   int nt;
@@ -291,7 +267,8 @@ __global__ __launch_bounds__(256, 4) void s1_stream2_kernel(S1Args p) {
   const int hc0 = nt * (NBW * 16);  // first h column of the workgroup
   const size_t ebase = (size_t)e * 2 * p.I;
 
-  // LDS: the scale rows as in s1_stream_kernel, then the other waves' sums [3][NB][64] v4f
+  // LDS: the tile's 16 activation scale rows, the 16 NBW gate and 16 NBW up weight
+  // scale rows, then the other waves' sums [KW - 1][NB][64] v4f
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int half = NBW * 16 * kb;
   const int tok = p.sorted[row0 + (c16 < nrows ? c16 : 0)] / p.k_total;
@@ -319,113 +296,36 @@ __global__ __launch_bounds__(256, 4) void s1_stream2_kernel(S1Args p) {
                 return p.xs + (size_t)t * kb;
               },
               kb, lane);
-        else if (kw == 1)
+        if (kw == KW / 4)
           dma_rows16(lds + 16 * kb + half, p.w13s + (ebase + p.I + hc0) * kb, half, lane);
-        else if (kw == 2)
+        if (kw == KW / 2)
           dma_rows16(lds + 16 * kb, p.w13s + (ebase + hc0) * kb, half, lane);
         wait_all_vmem();
         __syncthreads();
       });
-  v4f* red = reinterpret_cast<v4f*>(lds + (1 + 2 * NBW) * 16 * kb);
-  if (kw > 0) {
+  if constexpr (KW > 1) {
+    v4f* red = reinterpret_cast<v4f*>(lds + (1 + 2 * NBW) * 16 * kb);
+    if (kw > 0) {
 #pragma unroll
-    for (int n = 0; n < NB; ++n) red[((kw - 1) * NB + n) * 64 + lane] = acc[n];
+      for (int n = 0; n < NB; ++n) red[((kw - 1) * NB + n) * 64 + lane] = acc[n];
+    }
+    __syncthreads();
+    if (kw > 0) return;
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      acc[n] = acc[n] + red[n * 64 + lane];
+      if constexpr (KW == 4)
+        acc[n] = acc[n] + (red[(NB + n) * 64 + lane] + red[(2 * NB + n) * 64 + lane]);
+    }
   }
-  __syncthreads();
-  if (kw > 0) return;
-#pragma unroll
-  for (int n = 0; n < NB; ++n)
-    acc[n] = (acc[n] + red[n * 64 + lane]) + (red[(NB + n) * 64 + lane] + red[(2 * NB + n) * 64 + lane]);
   s1_epilogue<FA, NBW>(acc, p, row0, nrows, hc0, g, c16);
 }
 
-template <int FA, int J, int NBW, bool EVEN>
-__global__ __launch_bounds__(64) void s1_stream_kernel(S1Args p) {
-  static_assert(NBW % 2 == 0, "a quantisation block spans two 16-column tiles");
-  constexpr int NB = 2 * NBW;
-  constexpr int kAB = ActBytes<FA>::kBlock;
-  int4 tile;
-  int nt;
-  if (!tile_of_block(p.t, &tile, &nt)) return;
-  const int e = tile.x, row0 = tile.y, nrows = tile.z;
-  const int lane = threadIdx.x, g = lane >> 4, c16 = lane & 15;
-  const int kb = p.H / 32;
-  const int hc0 = nt * (NBW * 16);  // first h column of the wave
-  const size_t ebase = (size_t)e * 2 * p.I;
-
-  // LDS: the tile's 16 activation scale rows, then the wave's 16 NBW gate
-  // and 16 NBW up weight scale rows.
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  const int half = NBW * 16 * kb;  // bytes of the gate (or up) scale rows
-
-  const int tok = p.sorted[row0 + (c16 < nrows ? c16 : 0)] / p.k_total;
-  const uint8_t* a_row = p.xq + (size_t)tok * (p.H / 32) * kAB;
-  const uint8_t* b_rows[NB];
-  uint32_t wo[NB];
-#pragma unroll
-  for (int b = 0; b < NBW; ++b) {
-    const size_t gr = ebase + hc0 + 16 * b;  // first gate row of the group
-    b_rows[b] = p.w13 + gr * (p.H / 2) + 64 * c16;
-    b_rows[NBW + b] = p.w13 + (gr + p.I) * (p.H / 2) + 64 * c16;
-    wo[b] = (16 * b + c16) * kb;
-    wo[NBW + b] = (NBW * 16 + 16 * b + c16) * kb;
-  }
-  v4f acc[NB];
-#pragma unroll
-  for (int n = 0; n < NB; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-  stream_k<FA, J, NB, EVEN>(a_row, b_rows, kb / (4 * J), c16 * kb, 16 * kb, wo, g, acc, [&]() {
-    dma_gather16(
-        lds,
-        [&](int r) {
-          const int t = p.sorted[row0 + (r < nrows ? r : 0)] / p.k_total;
-          return p.xs + (size_t)t * kb;
-        },
-        kb, lane);
-    dma_rows16(lds + 16 * kb, p.w13s + (ebase + hc0) * kb, half, lane);
-    dma_rows16(lds + 16 * kb + half, p.w13s + (ebase + p.I + hc0) * kb, half, lane);
-  }, c16 < nrows);
-  s1_epilogue<FA, NBW>(acc, p, row0, nrows, hc0, g, c16);
-}
-
-template <int FA, int J, int NBW, bool EVEN>
-__global__ __launch_bounds__(64) void s2_stream_kernel(S2Args p) {
-  constexpr int NB = NBW;
-  constexpr int kAB = ActBytes<FA>::kBlock;
-  int4 tile;
-  int nt;
-  if (!tile_of_block(p.t, &tile, &nt)) return;
-  const int e = tile.x, row0 = tile.y, nrows = tile.z;
-  const int lane = threadIdx.x, g = lane >> 4, c16 = lane & 15;
-  const int kb = p.I / 32;
-  const int nc0 = nt * (NBW * 16);  // first output column of the wave
-  const size_t rbase = (size_t)e * p.H + nc0;
-
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  const size_t ar = (size_t)row0 + (c16 < nrows ? c16 : 0);
-  const uint8_t* a_row = p.hq + ar * (p.I / 32) * kAB;
-  const uint8_t* b_rows[NB];
-  uint32_t wo[NB];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    b_rows[b] = p.w2 + (rbase + 16 * b) * (p.I / 2) + 64 * c16;
-    wo[b] = (16 * b + c16) * kb;
-  }
-  v4f acc[NB];
-#pragma unroll
-  for (int n = 0; n < NB; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-  stream_k<FA, J, NB, EVEN>(a_row, b_rows, kb / (4 * J), c16 * kb, 16 * kb, wo, g, acc, [&]() {
-    dma_gather16(
-        lds, [&](int r) { return p.hs + ((size_t)row0 + (r < nrows ? r : 0)) * kb; }, kb, lane);
-    dma_rows16(lds + 16 * kb, p.w2s + rbase * kb, NB * 16 * kb, lane);
-  }, c16 < nrows);
-  s2_epilogue<NBW>(acc, p, row0, nrows, nc0, g, c16);
-}
-
-// Stage 2 with the K extent split over two waves (wave 0 stages the activation
-// scale rows, wave 1 the weight scale rows; partial = first half + second half,
-// the order that the fused down + combine repeats).
-template <int FA, int NBW>
-__global__ __launch_bounds__(128, 4) void s2_stream2_kernel(S2Args p) {
+// Stage 2, with the K extent split over two waves where split_k says so (wave 0
+// stages the activation scale rows, wave 1 the weight scale rows; partial = first
+// half + second half, the order that the fused down + combine repeats).
+template <int FA, int NBW, int KW>
+__global__ __launch_bounds__(64 * KW, 4) void s2_stream2_kernel(S2Args p) {
   constexpr int NB = NBW;
   constexpr int kAB = ActBytes<FA>::kBlock;
   int4 tile;
@@ -438,7 +338,8 @@ __global__ __launch_bounds__(128, 4) void s2_stream2_kernel(S2Args p) {
   const int nc0 = nt * (NBW * 16);  // first output column of the workgroup
   const size_t rbase = (size_t)e * p.H + nc0;
 
-  // LDS: the scale rows as in s2_stream_kernel, then wave 1's sums [NB][64] v4f
+  // LDS: the tile's 16 activation scale rows, the 16 NBW weight scale rows, then
+  // wave 1's sums [NB][64] v4f
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const uint32_t ar = (uint32_t)(row0 + (c16 < nrows ? c16 : 0));
   const uint8_t* wb[NB];
@@ -452,26 +353,27 @@ __global__ __launch_bounds__(128, 4) void s2_stream2_kernel(S2Args p) {
 #pragma unroll
   for (int n = 0; n < NB; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
   stream_lean<FA, NB>(
-      p.hq, ar * (uint32_t)(kb * kAB), wb, kw * (nst / 2), (kw + 1) * (nst / 2), c16 * kb, wo, lane,
+      p.hq, ar * (uint32_t)(kb * kAB), wb, kw * (nst / KW), (kw + 1) * (nst / KW), c16 * kb, wo, lane,
       acc, [&]() {
         if (kw == 0)
           dma_gather16(
               lds, [&](int r) { return p.hs + ((size_t)row0 + (r < nrows ? r : 0)) * kb; }, kb,
               lane);
-        else
-          dma_rows16(lds + 16 * kb, p.w2s + rbase * kb, NB * 16 * kb, lane);
+        if (kw == KW - 1) dma_rows16(lds + 16 * kb, p.w2s + rbase * kb, NB * 16 * kb, lane);
         wait_all_vmem();
         __syncthreads();
       });
-  v4f* red = reinterpret_cast<v4f*>(lds + (1 + NBW) * 16 * kb);
-  if (kw == 1) {
+  if constexpr (KW == 2) {
+    v4f* red = reinterpret_cast<v4f*>(lds + (1 + NBW) * 16 * kb);
+    if (kw == 1) {
 #pragma unroll
-    for (int n = 0; n < NB; ++n) red[n * 64 + lane] = acc[n];
+      for (int n = 0; n < NB; ++n) red[n * 64 + lane] = acc[n];
+    }
+    __syncthreads();
+    if (kw == 1) return;
+#pragma unroll
+    for (int n = 0; n < NB; ++n) acc[n] = acc[n] + red[n * 64 + lane];
   }
-  __syncthreads();
-  if (kw == 1) return;
-#pragma unroll
-  for (int n = 0; n < NB; ++n) acc[n] = acc[n] + red[n * 64 + lane];
   s2_epilogue<NBW>(acc, p, row0, nrows, nc0, g, c16);
 }
 
@@ -492,7 +394,7 @@ inline bool split_k(int kb) { return kb == 32 || kb == 64 || kb == 128 || kb == 
 // assignment index. After
 // one barrier the workgroup forms out[t, columns] = bf16(acc), acc =
 // fmaf(topk_w[t, j], P[t*k_total + j], acc) for j = 0, 1, ... -- the combine
-// kernel's arithmetic -- so the output has the bits of s2_stream_kernel +
+// kernel's arithmetic -- so the output has the bits of s2_stream2_kernel +
 // combine_kernel while no fp32 partial row reaches global memory.
 //
 // A wave streams about a dozen tiles one after another, each only a few K
@@ -673,7 +575,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void s2c_stream_kernel(S2CArgs c)
       const uint8_t* b_rows[1] = {p.w2 + rbase * (p.I / 2) + 64 * c16};
       const uint32_t wo[1] = {(uint32_t)(c16 * kb)};
       v4f acc[1] = {v4f{0.f, 0.f, 0.f, 0.f}};
-      stream_k<FA, J, 1, false>(
+      stream_k<FA, J, 1>(
           a_row, b_rows, kb / (4 * J), sb + c16 * kb, sb + 16 * kb, wo, g, acc, [&]() {
             dma_gather16(
                 lds + sb,
@@ -732,63 +634,38 @@ void launch_s2c_stream(const S2CArgs& p, int fa, hipStream_t s) {
   else launch_s2c<4>(p, s);
 }
 
-// Kernel instance: steps of 8 blocks (kb = K/32 a multiple of 16), else of
-// 4 with an even count (kb % 8 == 0), else a plain loop.
-template <typename K2, typename K1, typename K0, typename P>
-static void launch_stream(int kb, K2 k2, K1 k1, K0 k0, long mt, int ntl, const P& p0,
-                          hipStream_t s, size_t lds) {
-  P q = p0;
-  q.t.n_ntiles = ntl;
-  q.t.ngroup = n_group_of(ntl);
-  const long n = mt * ntl;
-  const dim3 grid((int)((n + 7) / 8 * 8));
-  if (kb % 16 == 0) hipLaunchKernelGGL(k2, grid, dim3(64), lds, s, q);
-  else if (kb % 8 == 0) hipLaunchKernelGGL(k1, grid, dim3(64), lds, s, q);
-  else hipLaunchKernelGGL(k0, grid, dim3(64), lds, s, q);
-}
-
 template <int FA, int NBW1>
 static void launch_s1(const S1Args& p, long mt, hipStream_t s) {
   const int kb = p.H / 32;
-  if (kb % 16 == 0 && kb >= 32) {
-    S1Args q = p;
-    const int ntl = p.I / (NBW1 * 16);
-    q.t.n_ntiles = ntl;
-    q.t.ngroup = n_group_of(ntl);
-    const long n = mt * ntl;
-    const size_t lds = (size_t)(1 + 2 * NBW1) * 16 * kb + (size_t)3 * 2 * NBW1 * 64 * 16;
-    hipLaunchKernelGGL((s1_stream2_kernel<FA, NBW1>), dim3((int)((n + 7) / 8 * 8)), dim3(256), lds,
-                       s, q);
-    return;
-  }
-  launch_stream(kb, s1_stream_kernel<FA, 2, NBW1, true>, s1_stream_kernel<FA, 1, NBW1, true>,
-                s1_stream_kernel<FA, 1, NBW1, false>, mt, p.I / (NBW1 * 16), p, s,
-                (size_t)(1 + 2 * NBW1) * 16 * kb);
+  S1Args q = p;
+  const int ntl = p.I / (NBW1 * 16);
+  q.t.n_ntiles = ntl;
+  q.t.ngroup = n_group_of(ntl);
+  const long n = mt * ntl;
+  const int kw = kb % 16 == 0 && kb >= 32 ? 4 : kb % 8 == 0 ? 2 : 1;
+  const size_t lds = (size_t)(1 + 2 * NBW1) * 16 * kb + (size_t)(kw - 1) * 2 * NBW1 * 64 * 16;
+  const auto k = kw == 4 ? s1_stream2_kernel<FA, NBW1, 4>
+                 : kw == 2 ? s1_stream2_kernel<FA, NBW1, 2> : s1_stream2_kernel<FA, NBW1, 1>;
+  hipLaunchKernelGGL(k, dim3((int)((n + 7) / 8 * 8)), dim3(64 * kw), lds, s, q);
 }
 
 template <int FA, int NBW2>
 static void launch_s2(const S2Args& p, long mt, hipStream_t s) {
   const int kb = p.I / 32;
-  if (split_k(kb)) {
-    S2Args q = p;
-    const int ntl = p.H / (NBW2 * 16);
-    q.t.n_ntiles = ntl;
-    q.t.ngroup = n_group_of(ntl);
-    const long n = mt * ntl;
-    const dim3 grid((int)((n + 7) / 8 * 8)), block(128);
-    const size_t lds = (size_t)(1 + NBW2) * 16 * kb + (size_t)NBW2 * 64 * 16;
-    hipLaunchKernelGGL((s2_stream2_kernel<FA, NBW2>), grid, block, lds, s, q);
-    return;
-  }
-  launch_stream(kb, s2_stream_kernel<FA, 2, NBW2, true>, s2_stream_kernel<FA, 1, NBW2, true>,
-                s2_stream_kernel<FA, 1, NBW2, false>, mt, p.H / (NBW2 * 16), p, s,
-                (size_t)(1 + NBW2) * 16 * kb);
+  S2Args q = p;
+  const int ntl = p.H / (NBW2 * 16);
+  q.t.n_ntiles = ntl;
+  q.t.ngroup = n_group_of(ntl);
+  const long n = mt * ntl;
+  const int kw = split_k(kb) ? 2 : 1;
+  const size_t lds = (size_t)(1 + NBW2) * 16 * kb + (size_t)(kw - 1) * NBW2 * 64 * 16;
+  const auto k = kw == 2 ? s2_stream2_kernel<FA, NBW2, 2> : s2_stream2_kernel<FA, NBW2, 1>;
+  hipLaunchKernelGGL(k, dim3((int)((n + 7) / 8 * 8)), dim3(64 * kw), lds, s, q);
 }
 
 // Stage 1: 32 h columns per workgroup, four waves splitting K where it is a
-// multiple of 512 from 1024 on, else one wave; stage 2: 64 output columns, two
-// waves for K = 1024, 2048, 4096 and 8192, else one. One wave steps 256 K
-// elements at a time (128 when K/32 is not a multiple of 16).
+// multiple of 512 from 1024 on, two where it is one of 256, else one; stage 2: 64
+// output columns, two waves for K = 1024, 2048, 4096 and 8192, else one.
 void launch_s1_stream(const S1Args& p, long mt, int fa, hipStream_t s) {
   if (fa == 0) launch_s1<0, 2>(p, mt, s);
   else if (fa == 2) launch_s1<2, 2>(p, mt, s);
