@@ -430,7 +430,7 @@ int moe_last_variant(void);
  * stage 1 of MOE_VARIANT_MIXED and MOE_VARIANT_SHORT). Not an operation
  * of the paper: a tuning and testing control. rows = 128: tiles of 128 rows,
  * two workgroups per CU; 256: tiles of 256 rows, one workgroup per CU;
- * 0 (the default): 128 when T * k_total / NE >= 192, else 256. Both give the
+ * 0 (the default): 128 when T * k_total / NE >= 216, else 256. Both give the
  * same bits (every output's K reduction is the same sequence of products).
  * Process-wide: it affects every later call on every thread and device; a
  * call that overlaps it may use either size. Other values return

@@ -13,7 +13,7 @@
 //
 // Two arrangements of the same code (gemm_tiled_body.h, compiled for each
 // TBM), chosen per call by the average rows per expert (tiled_rows):
-//  - TBM = 128 when experts average at least 192 rows (prefill): two
+//  - TBM = 128 when experts average at least 216 rows (prefill): two
 //    workgroups per CU (76 KiB of LDS each, a ring of two stages, the
 //    accumulators in 128 registers), so one workgroup's epilogue, ticket and
 //    set-up run under the other's products; a chunk of the work list holds up
@@ -85,8 +85,11 @@ namespace t128 {
 // Rows per expert (on average) from which the 128-row arrangement runs: it
 // keeps the matrix cores of two workgroups per CU busy when experts fill
 // their tiles, but tiles of fewer rows (the TP-shard shape) run better as
-// 256-row tiles with the row blocks split between the wave halves.
-constexpr long kRows128 = 192;
+// 256-row tiles with the row blocks split between the wave halves. Layer us at
+// H = 4096, I = 2048, top-8 + shared, 128- / 256-row tiles: 193 rows per expert
+// e4m3 1584 / 1537, e2m1 1429 / 1364; 210 rows 1613 / 1583, 1460 / 1392; 228 rows
+// 1719 / 1729, 1527 / 1495; 263 rows 1844 / 1893, 1640 / 1640.
+constexpr long kRows128 = 216;
 
 // 0: automatic; 128 or 256: forced (moe_set_tiled_rows).
 static std::atomic<int> g_tiled_rows{0};
