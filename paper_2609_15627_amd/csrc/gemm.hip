@@ -111,7 +111,10 @@ static Geometry geometry(const GemmArgs& a) {
     // 682 / 823 at 11.7 rows per expert, 894 / 883 at 17.5, 1280 / 940 at 28,
     // 1650 / 1070 at 38.5.
     Geometry g{};
-    g.s1_tiled = g.s2_tiled = A >= (long)kBf16TiledMinRows * a.NE;
+    if (A >= (long)kBf16TiledMinRows * a.NE) {
+      g.s1_tiled = bf16_lds_bytes(a.H) <= (size_t)max_lds_per_block();
+      g.s2_tiled = bf16_lds_bytes(a.I) <= (size_t)max_lds_per_block();
+    }
     return g;
   }
   const bool rows = A >= (long)kTiledMinRows * a.NE;

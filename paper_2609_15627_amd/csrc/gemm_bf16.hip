@@ -467,13 +467,15 @@ __global__ __launch_bounds__(64 * KW) void bf16_stream_kernel(BfArgs p) {
 
 int bf16_rows() { return kBM; }
 
+size_t bf16_lds_bytes(int K) { return (size_t)2 * kBSlot + (size_t)256 * bb_stride(K / 32); }
+
 template <int ST>
 static void launch_bf(const BfArgs& p0, long mt, int n_ntiles, hipStream_t s) {
   BfArgs p = p0;
   p.t.n_ntiles = n_ntiles;
   p.t.ngroup = n_group_of(n_ntiles);
   const long n = mt * n_ntiles;
-  const size_t lds = (size_t)2 * kBSlot + (size_t)256 * bb_stride(p.K / 32);
+  const size_t lds = bf16_lds_bytes(p.K);
   hipLaunchKernelGGL((bf16_block_kernel<ST>), dim3((int)((n + 7) / 8 * 8)), dim3(256), lds, s, p);
 }
 
@@ -505,9 +507,11 @@ static void launch_bf_stream(const BfArgs& p0, long mt, int ntl, hipStream_t s) 
   p.t.ngroup = n_group_of(ntl);
   constexpr int NB = ST == 1 ? 2 * NBW : NBW;
   const long n = mt * ntl;
-  const int kw = bf_split(p.K);
+  int kw = bf_split(p.K);
   const dim3 grid((int)((n + 7) / 8 * 8));
-  const size_t lds = (size_t)NB * 16 * (p.K / 32) + (size_t)(kw - 1) * NB * 64 * 16;
+  auto lds_of = [&](int v) { return (size_t)NB * 16 * (p.K / 32) + (size_t)(v - 1) * NB * 64 * 16; };
+  if (kw == 4 && lds_of(4) > kLdsBytes) kw = 2;  // very long rows: the scales take the LDS
+  const size_t lds = lds_of(kw);
   const auto k = kw == 4 ? bf16_stream_kernel<ST, NBW, 4>
                  : kw == 2 ? bf16_stream_kernel<ST, NBW, 2> : bf16_stream_kernel<ST, NBW, 1>;
   hipLaunchKernelGGL(k, grid, dim3(64 * kw), lds, s, p);

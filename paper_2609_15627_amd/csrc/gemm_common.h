@@ -97,6 +97,8 @@ __device__ __forceinline__ uint32_t gather_scales(const uint8_t* p, int g) {
   return r;
 }
 
+constexpr size_t kLdsBytes = 160 * 1024;  // LDS of a CU, and the most of a workgroup
+
 constexpr int kQueueInts = 16;  // ints of the persistent geometry's work queue
 
 struct TileArgs {

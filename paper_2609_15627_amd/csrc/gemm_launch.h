@@ -21,6 +21,7 @@ void launch_s2c_stream(const S2CArgs& p, int fa, hipStream_t s);
 // BF16 contract (bf16 activations, FP4 weights expanded to bf16 in
 // registers, bf16 intermediate): row tiles of bf16_rows() rows.
 int bf16_rows();
+size_t bf16_lds_bytes(int K);
 void launch_s1_bf16(const S1Args& p, long mt, hipStream_t s);
 void launch_s2_bf16(const S2Args& p, long mt, hipStream_t s);
 // ... and its weight-streaming geometry for few rows per expert (tiles of 16

@@ -642,8 +642,12 @@ static void launch_s1(const S1Args& p, long mt, hipStream_t s) {
   q.t.n_ntiles = ntl;
   q.t.ngroup = n_group_of(ntl);
   const long n = mt * ntl;
-  const int kw = kb % 16 == 0 && kb >= 32 ? 4 : kb % 8 == 0 ? 2 : 1;
-  const size_t lds = (size_t)(1 + 2 * NBW1) * 16 * kb + (size_t)(kw - 1) * 2 * NBW1 * 64 * 16;
+  int kw = kb % 16 == 0 && kb >= 32 ? 4 : kb % 8 == 0 ? 2 : 1;
+  auto lds_of = [&](int v) {
+    return (size_t)(1 + 2 * NBW1) * 16 * kb + (size_t)(v - 1) * 2 * NBW1 * 64 * 16;
+  };
+  if (lds_of(kw) > kLdsBytes) kw = 1;  // very long rows: the scales take the LDS
+  const size_t lds = lds_of(kw);
   const auto k = kw == 4 ? s1_stream2_kernel<FA, NBW1, 4>
                  : kw == 2 ? s1_stream2_kernel<FA, NBW1, 2> : s1_stream2_kernel<FA, NBW1, 1>;
   hipLaunchKernelGGL(k, dim3((int)((n + 7) / 8 * 8)), dim3(64 * kw), lds, s, q);

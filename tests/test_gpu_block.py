@@ -72,3 +72,27 @@ def test_bf16_row_block(m, T, H, I, E, k, S, routing):
     layer, out = run(m, cfg, inp)
     assert m.moe_last_variant() == m.VARIANT_BF16
     check(cfg, inp, layer, out, np.arange(cfg.T))
+
+
+@pytest.mark.parametrize("T,H,I,E,k,fmt,variant", [
+    (40, 16384, 128, 2, 1, "bf16", "BF16_STREAM"),  # row-block by rows, but its scales exceed LDS
+    (40, 15360, 128, 2, 1, "bf16", "BF16"),         # the longest rows that fit
+    (3, 61440, 128, 2, 1, "e4m3", "STREAM"),        # the split's sums no longer fit beside the scales
+    (3, 77824, 128, 2, 1, "bf16", "BF16_STREAM"),
+])
+def test_long_rows(m, T, H, I, E, k, fmt, variant):
+    """K extents whose scale rows take most of a workgroup's LDS."""
+    cfg = synth.LayerConfig("long", T, H, E, k, I, 0, "normal", 9)
+    inp = synth.make_inputs(cfg)
+    log(f"long rows {(T, H, I, E, k, fmt)}")
+    w = gc.dev_expert_weights(inp.weights)
+    layer, out = run_layer(m, cfg, gc.to_dev_bf16(inp.x), w, logits=inp.logits, fmt=fmt)
+    assert m.moe_last_variant() == getattr(m, "VARIANT_" + variant)
+    if fmt == "bf16":
+        # bf16 output rounding 2^-8 + 1e-3 for h one bf16 step off; the share of such
+        # h grows with the fp32 sums' length (sqrt(K)), so it has no bound of its own
+        from oracle import moe as omoe
+        ref = omoe.layer(inp.x, *inp.weights, k=k, logits=inp.logits, fmt="bf16")
+        assert gc.rowrel(gc.bf16_to_f64(gc.bf16_bits(out)), ref["out_f64"]) <= 5e-3
+    else:
+        check_against_oracle(cfg, inp, layer, out, np.arange(T), fmt)
