@@ -254,7 +254,7 @@ def measure_router(cfg, steps):
     w = torch.empty((cfg.T, kt), dtype=torch.float32, device=dev)
     lg = torch.empty((cfg.T, cfg.E), dtype=torch.float32, device=dev)
 
-    def fused():  # one call; with a logits buffer the library picks its path by T
+    def fused():  # one call; with a logits buffer it runs both kernels
         moe.moe_router_topk(x, wr, cfg.k, cfg.n_shared, logits=lg, topk_ids=ids, topk_w=w)
 
     def two_call():
@@ -275,7 +275,7 @@ def measure_router(cfg, steps):
         torch.cuda.synchronize()
         out[name] = t0.elapsed_time(t1) / n
     nbytes = cfg.T * cfg.H * 2 + cfg.E * cfg.H * 2 + cfg.T * kt * 8
-    out["path"] = "fused" if cfg.T >= 1024 else "logits kernel + routing kernel"
+    out["path"] = "logits kernel + routing kernel"
     out["router_topk_GBps"] = nbytes / (out["router_topk_ms"] * 1e-3) / 1e9
     out["router_topk_TFLOPs"] = 2.0 * cfg.T * cfg.H * cfg.E / (out["router_topk_ms"] * 1e-3) / 1e12
     return out
