@@ -396,7 +396,7 @@ moe_status moe_combine_fixed_order(const float* partials, const float* topk_w, i
  * Small batches (T * (k + n_shared) <= 1024, n_experts_total <= 512, not the
  * LDS-tiled geometry) sort, build the tile lists and quantise x in one launch,
  * up to 16 tokens with the routing; up to 98304 assignments these steps take
- * three launches with the routing. */
+ * three launches with the routing (E <= 512 where the routing joins). */
 typedef struct {
   int T, H, E, k, n_shared, I, n_experts_total; /* E: columns of the logits */
   moe_act_format f;

@@ -398,8 +398,8 @@ moe_status moe_layer_forward(const moe_layer_args* a, void* stream) {
   if (a->w_router)
     e = moe::launch_router_logits(a->x, a->w_router, T, a->H, a->E, a->logits_buf, s);
   int stages = 7;
-  const bool large = moe::front_large_ok(g), front = large || moe::front_ok(g);
-  const bool routes = large || (front && moe::front_routes(T));
+  const bool large = moe::front_large_ok(g, a->E), front = large || moe::front_ok(g);
+  const bool routes = large || (front && moe::front_routes(T, a->E));
   if (e == hipSuccess && !routes)
     e = moe::launch_route_topk(logits, T, a->E, a->k, a->n_shared, a->topk_ids, a->topk_w, s);
   if (e != hipSuccess) return launched(e);

@@ -32,6 +32,10 @@ __device__ __forceinline__ void front_tiles(const TileArgs& t, int BM, int NE, i
   if (threadIdx.x == 0) *const_cast<int*>(t.ntiles) = total;
 }
 
+// Logits a lane group of these kernels holds; a router may have more columns than
+// there are experts (an id past the last one is left out of the sort).
+constexpr int kFrontE = 8 * kWave;
+
 // EPL: experts per lane of the routing, 0: the ids are given.
 template <int FMT, int EPL>
 __global__ __launch_bounds__(1024) void front_kernel(FrontArgs a) {
@@ -78,7 +82,7 @@ bool front_sizes_ok(int T, int NE, int k_total) {
   return T > 0 && (long)T * k_total <= kChunk && NE <= kSmallNE;
 }
 
-bool front_routes(int T) { return T <= kFrontTokens; }
+bool front_routes(int T, int E) { return T <= kFrontTokens && E <= kFrontE; }
 
 hipError_t launch_front(const FrontArgs& a0, hipStream_t s) {
   FrontArgs a = a0;
@@ -171,9 +175,9 @@ static void launch_route_quant(const FrontArgs& a, hipStream_t s) {
   else hipLaunchKernelGGL((route_quant_kernel<FMT, 8>), grid, block, 0, s, a, nrb);
 }
 
-bool front_large_sizes_ok(int T, int NE, int k_total) {
+bool front_large_sizes_ok(int T, int NE, int k_total, int E) {
   const long A = (long)T * k_total;
-  return A > kChunk && A <= (long)kFrontChunks * kChunk && NE <= kSmallNE;
+  return E <= kFrontE && A > kChunk && A <= (long)kFrontChunks * kChunk && NE <= kSmallNE;
 }
 
 hipError_t launch_front_large(const FrontArgs& a0, hipStream_t s) {

@@ -167,7 +167,9 @@ bool front_ok(const GemmArgs& a) {
   return front_sizes_ok(a.T, a.NE, a.k_total) && (a.fmt == kFmtBf16 || (!g.s1_tiled && !g.s2_tiled));
 }
 
-bool front_large_ok(const GemmArgs& a) { return front_large_sizes_ok(a.T, a.NE, a.k_total); }
+bool front_large_ok(const GemmArgs& a, int E) {
+  return front_large_sizes_ok(a.T, a.NE, a.k_total, E);
+}
 
 hipError_t launch_front_steps(const GemmArgs& a, const FrontIO& io, hipStream_t s) {
   const GemmWorkspace w = gemm_workspace(a.T, a.H, a.I, a.NE, a.k_total, a.fmt);

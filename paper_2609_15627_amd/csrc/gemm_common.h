@@ -151,9 +151,9 @@ struct FrontArgs {
 };
 constexpr int kFrontTokens = 16;  // tokens up to which the launch routes too
 bool front_sizes_ok(int T, int NE, int k_total);
-bool front_routes(int T);
+bool front_routes(int T, int E);
 hipError_t launch_front(const FrontArgs& a, hipStream_t s);
-bool front_large_sizes_ok(int T, int NE, int k_total);
+bool front_large_sizes_ok(int T, int NE, int k_total, int E);
 hipError_t launch_front_large(const FrontArgs& a, hipStream_t s);
 
 struct S1Args {

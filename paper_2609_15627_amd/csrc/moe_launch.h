@@ -78,8 +78,8 @@ struct FrontIO {
   int32_t* hist;  // permutation workspace (front_large_ok)
 };
 bool front_ok(const GemmArgs& a);
-bool front_large_ok(const GemmArgs& a);
-bool front_routes(int T);
+bool front_large_ok(const GemmArgs& a, int E);
+bool front_routes(int T, int E);
 hipError_t launch_front_steps(const GemmArgs& a, const FrontIO& io, hipStream_t s);
 // Per-chunk expert histograms of the assignments (hist [chunks, NE]).
 hipError_t launch_perm_hist(const int32_t* ids, int A, int NE, int32_t* hist, hipStream_t s);

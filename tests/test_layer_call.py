@@ -100,3 +100,28 @@ def test_empty_batch(m):
                             logits=torch.empty((0, 8), device="cuda"))
         torch.cuda.synchronize()
         assert out.shape == (0, 256) and not layer.perm[1].any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T", [4, 600])
+def test_more_router_columns_than_experts(m, T):
+    """600 logits for 9 experts: ids past the last expert are left out alike."""
+    log(f"layer call, 600 router columns, {T} tokens")
+    cfg = synth.LayerConfig("wide", T, 256, 8, 2, 128, 1, "normal", 5)
+    inp = synth.make_inputs(cfg)
+    w, x = gc.dev_expert_weights(inp.weights), gc.to_dev_bf16(inp.x)
+    lg = np.random.default_rng(T).standard_normal((T, 600)).astype(np.float32)
+    lg[::2, 599] = 9.0  # a choice past column 512
+    lg[1::2, 3] = 9.0
+    lg = torch.from_numpy(lg).cuda()
+    one, sep = (m.MoELayer(T, 256, 8, 2, 128, 1, "e4m3") for _ in range(2))
+    for layer in (one, sep):
+        layer.partials.zero_()  # rows of the left-out ids stay as they are
+    one.forward(x, w, logits=lg)
+    sep.forward(x, w, logits=lg, events=[torch.cuda.Event(enable_timing=True) for _ in range(7)])
+    torch.cuda.synchronize()
+    assert (one.ids[::2] == 599).any(1).all()
+    for n in ("ids", "w", "out"):
+        assert torch.equal(getattr(one, n), getattr(sep, n)), n
+    for i in (0, 1):
+        assert torch.equal(one.perm[i], sep.perm[i])
